@@ -9,11 +9,13 @@
 //
 // A neighbour u is claimed with one compare-and-swap on dist[u] (-1 -> L + 1),
 // so each node enters exactly one frontier, once.  Nodes of degree up to 32
-// expand with one thread; wider ones are handed to a wavefront of the same
-// workgroup.  Pushes go to the workgroup's own segment (shared-memory counter,
+// expand with one thread, nodes up to kHubDeg entries with a wavefront of the
+// same workgroup, and wider ones (hubs) by the whole grid in a second step of
+// the level.  Pushes go to the workgroup's own segment (shared-memory counter,
 // no global atomic); a segment that fills up spills into an overflow list
 // through one atomicAdd per spilled node.  All levels run in one cooperative
-// launch with the grid barrier of the coloring kernels.
+// launch with the grid barrier of the coloring kernels, one barrier per level
+// and one more in levels with hubs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,6 +33,22 @@ namespace bfs {
 constexpr int kBlock = 1024;
 constexpr int kLightDeg = 32;     // wider frontier nodes are expanded by a wavefront
 constexpr int kHeavyPerBlock = 1024;
+// Rows longer than this are spread over the grid.  A wavefront takes about 1.5 us per 256 entries
+// (column id, distance, claim: three dependent trips to memory), so a row of this length keeps it for
+// about 12 us, what the extra barrier and the staging of the hub step cost; the widest row of an
+// R-MAT graph of 2^22 nodes (160 000 entries) kept one for 4 ms.
+constexpr int kHubDeg = 2048;
+constexpr int kHubChunk = 4 * kWave;  // hub entries per wavefront step
+
+// Control block of one call: cleared before it, read back after it.
+struct BfsCtl {
+    int32_t levels;       // non-empty levels
+    int32_t done;         // the last level was empty (stays 0 if a grid-barrier wait gave up)
+    int32_t bad;          // decreasing row pointers, or a column id out of range
+    int32_t bad_ends;     // rowptr[0] != 0 or rowptr[n] != m
+    int32_t ovf_cnt[3];   // three rotating overflow sizes: level L reads L % 3, fills (L + 1) % 3
+    int32_t hubs[3];      // three rotating hub counts: level L uses L % 3
+};
 
 struct BfsDev {
     const int32_t *rowptr;
@@ -39,13 +57,15 @@ struct BfsDev {
     int32_t *seg[2];      // frontier lists: grid segments of cap entries
     int32_t *seg_cnt[2];  // entries per segment (at most cap)
     int32_t *ovf[2];      // overflow lists
-    int32_t *ovf_cnt;     // three rotating overflow sizes: level L reads L % 3, fills (L + 1) % 3
+    int32_t *hub;         // hubs of the level (at most m / (kHubDeg + 1))
     int32_t *trace;       // frontier size per level
     int64_t trace_cap;
     int64_t n;
+    int64_t m;
     int64_t threshold;    // topology-driven level iff |frontier| > threshold
+    int32_t source;
     int32_t cap;
-    int32_t *levels;      // out: non-empty levels (stays -1 if a grid-barrier wait gave up)
+    BfsCtl *ctl;
     Barrier *bar;
     uint64_t bar_limit;   // wall-clock ticks a grid-barrier wait may last
 };
@@ -55,7 +75,7 @@ __device__ int32_t frontier_view(const BfsDev &d, int p, int lvl, int32_t *pre) 
     const int nb = gridDim.x;
     int x = 0;
     if (threadIdx.x < (unsigned)nb) x = d.seg_cnt[p][threadIdx.x];
-    else if (threadIdx.x == (unsigned)nb) x = d.ovf_cnt[lvl % 3];
+    else if (threadIdx.x == (unsigned)nb) x = d.ctl->ovf_cnt[lvl % 3];
     int tot;
     const int ex = block_scan(x, &tot);
     if (threadIdx.x <= (unsigned)nb) pre[threadIdx.x] = ex;
@@ -75,19 +95,72 @@ __device__ __forceinline__ int32_t frontier_at(const BfsDev &d, int p, const int
     return d.seg[p][(int64_t)lo * d.cap + (i - pre[lo])];
 }
 
-// Claims u for level `next`; the winner appends it to this workgroup's segment (or the overflow list).
-__device__ __forceinline__ void visit(const BfsDev &d, int32_t u, int32_t next, int dst, int *s_cnt) {
-    if (__hip_atomic_load(&d.dist[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != -1) return;
-    if (atomicCAS(&d.dist[u], -1, next) != -1) return;
-    const int p = atomicAdd(s_cnt, 1);
-    if (p < d.cap) d.seg[dst][(int64_t)blockIdx.x * d.cap + p] = u;
-    else d.ovf[dst][atomicAdd(&d.ovf_cnt[next % 3], 1)] = u;
+// Row entries k0, k0 + step, ... (P of them) below e: claims their unvisited nodes for level `next`.  The
+// P loads of each kind are in flight together.  A first look at dist reads through the caches: a value
+// other than -1 is final, a stale -1 only leads to the second look, which does not (most entries of a
+// large level lead to nodes reached long before, and those are settled in the caches).  Winners go to
+// this workgroup's segment, or to the overflow list.
+template <int P>
+__device__ __forceinline__ void visit(const BfsDev &d, int64_t k0, int32_t step, int64_t e, int32_t next, int dst,
+                                      int *s_cnt) {
+    int32_t u[P];
+    bool open[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) u[j] = k0 + j * step < e ? d.colidx[k0 + j * step] : -1;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+        open[j] = u[j] >= 0 && __hip_atomic_load(&d.dist[u[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == -1;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+        if (open[j]) open[j] = __hip_atomic_load(&d.dist[u[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == -1;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        if (!open[j] || atomicCAS(&d.dist[u[j]], -1, next) != -1) continue;
+        const int p = atomicAdd(s_cnt, 1);
+        if (p < d.cap) d.seg[dst][(int64_t)blockIdx.x * d.cap + p] = u[j];
+        else d.ovf[dst][atomicAdd(&d.ctl->ovf_cnt[next % 3], 1)] = u[j];
+    }
+}
+
+// Hub step of a level: the rows of its `hubs` hubs in chunks of kHubChunk entries over every wavefront of
+// the grid.  Each workgroup stages up to kBlock hubs at a time (row bounds, chunk prefix sums).
+__device__ void expand_hubs(const BfsDev &d, int32_t hubs, int32_t next, int dst, int *s_cnt) {
+    __shared__ int32_t s_b[kBlock], s_e[kBlock], s_pre[kBlock + 1];
+    const int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
+    for (int32_t h0 = 0; h0 < hubs; h0 += kBlock) {
+        const int32_t h = h0 + threadIdx.x;
+        int chunks = 0;
+        if (h < hubs) {
+            const int32_t v = d.hub[h];
+            s_b[threadIdx.x] = d.rowptr[v];
+            s_e[threadIdx.x] = d.rowptr[v + 1];
+            chunks = (int)(((int64_t)s_e[threadIdx.x] - s_b[threadIdx.x] + kHubChunk - 1) / kHubChunk);
+        }
+        int total;
+        s_pre[threadIdx.x] = block_scan(chunks, &total);
+        if (threadIdx.x == 0) s_pre[kBlock] = total;
+        __syncthreads();
+        const int nh = min(kBlock, hubs - h0);
+        for (int64_t g = gw; g < total; g += nw) {
+            int lo = 0, hi = nh;  // hub lo with s_pre[lo] <= g < s_pre[lo + 1]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_pre[mid] <= g) lo = mid;
+                else hi = mid;
+            }
+            const int64_t k0 = s_b[lo] + (g - s_pre[lo]) * kHubChunk;
+            visit<kHubChunk / kWave>(d, k0 + lane_id(), kWave, s_e[lo], next, dst, s_cnt);
+        }
+        __syncthreads();
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
     __shared__ int32_t pre[kMaxRoundBlocks + 2];
     __shared__ int32_t heavy[kHeavyPerBlock];
-    __shared__ int s_cnt, s_heavy;
+    __shared__ int s_cnt, s_heavy, s_hubs;
+    if (d.ctl->bad | d.ctl->bad_ends) return;  // every workgroup reads the same flags: no row is read
     GridBarrier gb;
     if (!gb.setup(d.bar, d.bar_limit)) return;
     const int64_t nt = (int64_t)gridDim.x * blockDim.x;
@@ -98,8 +171,13 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
         const int32_t size = frontier_view(d, src, lvl, pre);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             if (lvl < d.trace_cap) d.trace[lvl] = size;
-            if (size == 0) *d.levels = lvl;
-            d.ovf_cnt[(lvl + 2) % 3] = 0;  // the overflow size level lvl + 1 fills (read last at level lvl - 1)
+            if (size == 0) {
+                d.ctl->levels = lvl;
+                d.ctl->done = 1;
+            }
+            // counts of level lvl + 1: last read before the barrier that ended level lvl - 1
+            d.ctl->ovf_cnt[(lvl + 2) % 3] = 0;
+            d.ctl->hubs[(lvl + 1) % 3] = 0;
         }
         if (size == 0) break;
         const bool topo = (int64_t)size > d.threshold;
@@ -110,7 +188,8 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
             s_heavy = 0;
         }
         __syncthreads();
-        if (!gb.sync()) return;  // every part of the frontier is read before any segment of the next one is written
+        // No barrier here: this level fills the lists and counts of parity dst, last read in level
+        // lvl - 1, which every workgroup has left.
         for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < items; i0 += nt) {
             const int64_t i = i0 + threadIdx.x;
             int32_t v = -1;
@@ -120,22 +199,17 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
             }
             if (v >= 0) {
                 const int32_t b = d.rowptr[v], e = d.rowptr[v + 1];
-                if (e - b > kLightDeg) {
-                    const int h = atomicAdd(&s_heavy, 1);
-                    if (h < kHeavyPerBlock) heavy[h] = v;
-                    else v = -2;  // the list is full: expand it here
-                }
-                if (e - b <= kLightDeg || v == -2) {
-                    for (int32_t k = b; k < e; ++k) visit(d, d.colidx[k], next, dst, &s_cnt);
-                }
+                if (e - b > kHubDeg) d.hub[atomicAdd(&d.ctl->hubs[lvl % 3], 1)] = v;
+                else if (e - b > kLightDeg) heavy[atomicAdd(&s_heavy, 1)] = v;  // at most a workgroup's threads
+                else
+                    for (int64_t k = b; k < e; k += 4) visit<4>(d, k, 1, e, next, dst, &s_cnt);
             }
-            // the heavy list fills up at most blockDim entries per pass: drain it before the next
             __syncthreads();
-            const int nh = min(s_heavy, kHeavyPerBlock);
+            const int nh = s_heavy;
             for (int h = w; h < nh; h += nwv) {
                 const int32_t u = heavy[h];
                 const int32_t b = d.rowptr[u], e = d.rowptr[u + 1];
-                for (int32_t k = b + lane; k < e; k += kWave) visit(d, d.colidx[k], next, dst, &s_cnt);
+                for (int64_t k = b; k < e; k += 4 * kWave) visit<4>(d, k + lane, kWave, e, next, dst, &s_cnt);
             }
             __syncthreads();
             if (threadIdx.x == 0) s_heavy = 0;
@@ -143,30 +217,61 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
         }
         if (threadIdx.x == 0) d.seg_cnt[dst][blockIdx.x] = min(s_cnt, d.cap);
         if (!gb.sync()) return;
+        if (threadIdx.x == 0) s_hubs = (int32_t)ld_agent((unsigned *)&d.ctl->hubs[lvl % 3]);
+        __syncthreads();
+        const int32_t hubs = s_hubs;
+        if (hubs > 0) {  // the same in every workgroup
+            expand_hubs(d, hubs, next, dst, &s_cnt);
+            if (threadIdx.x == 0) d.seg_cnt[dst][blockIdx.x] = min(s_cnt, d.cap);
+            if (!gb.sync()) return;
+        }
     }
 }
 
 // Buffers of one device, kept between calls (they only grow).
 struct BfsWorkspace {
-    DBuf<int32_t> seg0, seg1, cnt0, cnt1, ovf0, ovf1, ovfc, tr, lv, bad;
+    DBuf<int32_t> seg0, seg1, cnt0, cnt1, ovf0, ovf1, hub, tr;
+    DBuf<BfsCtl> ctl;
     DBuf<Barrier> bar;
+    BfsCtl *host_ctl = nullptr;  // pinned
 };
 std::mutex g_bfs_mutex;
 std::vector<BfsWorkspace> g_bfs_ws;
 
-// Row pointers non-decreasing inside [0, m] and every column id inside [0, n).
-__global__ __launch_bounds__(256) void k_bfs_check(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m,
-                                                   int32_t *bad) {
-    int b = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t a = rowptr[v], e = rowptr[v + 1];
-        if (a < 0 || e < a || e > m) {
-            b = 1;
-            continue;
-        }
-        for (int64_t k = a; k < e; ++k) b |= colidx[k] < 0 || colidx[k] >= n;
+// Initial state (the source at distance 0 and alone in the frontier, every other node unreached) and the
+// input checks: the CSR ends, row pointers non-decreasing inside [0, m] and, with `ids`, every entry's
+// column id inside [0, n).  The rows cover exactly the m entries when the row pointers pass, so the
+// entries are read as one array, coalesced, whatever the degrees; a lane per row kept one lane for the
+// 160 000 entries of the widest row of an R-MAT graph of 2^22 nodes (16.5 ms).
+__global__ __launch_bounds__(256) void k_bfs_prep(BfsDev d, int32_t ids) {
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
+    if (gt == 0) {
+        d.seg[0][0] = d.source;
+        if (d.rowptr[0] != 0 || d.rowptr[d.n] != d.m) d.ctl->bad_ends = 1;
     }
-    if (__ballot(b) && lane_id() == 0) *bad = 1;
+    for (int64_t i = gt; i < kMaxRoundBlocks; i += nt) {
+        d.seg_cnt[0][i] = i == 0;
+        d.seg_cnt[1][i] = 0;
+    }
+    int b = 0;
+    for (int64_t v = gt; v < d.n; v += nt) {
+        d.dist[v] = v == d.source ? 0 : -1;
+        if (ids) {
+            const int64_t a = d.rowptr[v], e = d.rowptr[v + 1];
+            b |= a < 0 || e < a || e > d.m;
+        }
+    }
+    if (ids) {
+        const uint32_t n = (uint32_t)d.n;
+        for (int64_t k = gt; k < d.m; k += 8 * nt) {
+            uint32_t u[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) u[j] = k + j * nt < d.m ? (uint32_t)d.colidx[k + j * nt] : 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) b |= u[j] >= n;  // negative ids too
+        }
+    }
+    if (__ballot(b) && lane_id() == 0) d.ctl->bad = 1;
 }
 
 }  // namespace bfs
@@ -179,19 +284,17 @@ void release_bfs_workspaces() {
         if (hipSetDevice((int)dv) != hipSuccess) continue;
         bfs::BfsWorkspace &w = bfs::g_bfs_ws[dv];
         w.seg0.release(); w.seg1.release(); w.cnt0.release(); w.cnt1.release(); w.ovf0.release(); w.ovf1.release();
-        w.ovfc.release(); w.tr.release(); w.lv.release(); w.bad.release(); w.bar.release();
+        w.hub.release(); w.tr.release(); w.ctl.release(); w.bar.release();
+        if (w.host_ctl) (void)hipHostFree(w.host_ctl);
     }
     (void)hipSetDevice(cur);
     bfs::g_bfs_ws.clear();
 }
 
-}  // namespace ipgc
+namespace bfs {
 
-extern "C" int ipgc_bfs(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m, int64_t source, int mode,
-                        const ipgc_options *options, void *stream, int32_t *out_dist, int32_t *out_levels,
-                        ipgc_trace *trace) {
-    using namespace ipgc;
-    using namespace ipgc::bfs;
+int bfs_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m, int64_t source, int mode,
+             const ipgc_options *options, hipStream_t s, int32_t *out_dist, int32_t *out_levels, ipgc_trace *trace) {
     if (!out_levels) return fail(IPGC_EINVAL, "null out_levels");
     *out_levels = -1;
     if (n < 0 || m < 0) return fail(IPGC_EINVAL, "negative n or m");
@@ -208,13 +311,6 @@ extern "C" int ipgc_bfs(const int32_t *rowptr, const int32_t *colidx, int64_t n,
     }
     if (source < 0 || source >= n) return fail(IPGC_EINVAL, "source %lld outside [0, n)", (long long)source);
     if (!rowptr || !out_dist || (m > 0 && !colidx)) return fail(IPGC_EINVAL, "null device pointer");
-    hipStream_t s = (hipStream_t)stream;
-    int32_t ends[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(&ends[0], rowptr, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&ends[1], rowptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (ends[0] != 0 || ends[1] != m) return fail(IPGC_EBADCSR, "rowptr[0] != 0 or rowptr[n] != m");
-
     int dev = 0, cus = 0, per_cu = 0, coop = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
@@ -234,99 +330,75 @@ extern "C" int ipgc_bfs(const int32_t *rowptr, const int32_t *colidx, int64_t n,
     std::lock_guard<std::mutex> lock(g_bfs_mutex);
     if ((int)g_bfs_ws.size() <= dev) g_bfs_ws.resize(dev + 1);
     BfsWorkspace &w = g_bfs_ws[dev];
-    DBuf<int32_t> &seg0 = w.seg0, &seg1 = w.seg1, &cnt0 = w.cnt0, &cnt1 = w.cnt1, &ovf0 = w.ovf0, &ovf1 = w.ovf1,
-                  &ovfc = w.ovfc, &tr = w.tr, &lv = w.lv, &bad = w.bad;
-    DBuf<Barrier> &bar = w.bar;
+    const int32_t cap = (int32_t)((n + grid - 1) / grid) + kBlock;
+    const int64_t seg_len = (int64_t)grid * cap;
+    TRY(w.seg0.reserve(seg_len));
+    TRY(w.seg1.reserve(seg_len));
+    TRY(w.cnt0.reserve(kMaxRoundBlocks));
+    TRY(w.cnt1.reserve(kMaxRoundBlocks));
+    TRY(w.ovf0.reserve(n));
+    TRY(w.ovf1.reserve(n));
+    TRY(w.hub.reserve(m / (kHubDeg + 1) + 1));
+    TRY(w.tr.reserve(n + 1));
+    TRY(w.ctl.reserve(1));
+    TRY(w.bar.reserve(1));
+    if (!w.host_ctl) HIP_TRY(hipHostMalloc(&w.host_ctl, sizeof(BfsCtl), hipHostMallocDefault));
     BfsDev d{};
-    d.cap = (int32_t)((n + grid - 1) / grid) + kBlock;
-    const int64_t seg_len = (int64_t)grid * d.cap;
-    int rc = IPGC_OK;
-    do {
-        if ((rc = seg0.reserve(seg_len)) || (rc = seg1.reserve(seg_len)) || (rc = cnt0.reserve(kMaxRoundBlocks)) ||
-            (rc = cnt1.reserve(kMaxRoundBlocks)) || (rc = ovf0.reserve(n)) || (rc = ovf1.reserve(n)) ||
-            (rc = ovfc.reserve(3)) || (rc = tr.reserve(n + 1)) || (rc = lv.reserve(1)) || (rc = bad.reserve(1)) ||
-            (rc = bar.reserve(1)))
-            break;
-        // ids in range and rows non-decreasing (the kernel reads rows through them)
-        if (P.check_ids) {
-            int32_t h_bad = 0;
-            if (hipMemsetAsync(bad.p, 0, sizeof(int32_t), s) != hipSuccess) {
-                rc = fail(IPGC_EHIP, "BFS set-up failed");
-                break;
-            }
-            k_bfs_check<<<(int)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, s>>>(rowptr, colidx, n, m, bad.p);
-            if (hipGetLastError() != hipSuccess ||
-                hipMemcpyAsync(&h_bad, bad.p, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipStreamSynchronize(s) != hipSuccess) {
-                rc = fail(IPGC_EHIP, "BFS checks failed to run");
-                break;
-            }
-            if (h_bad) {
-                rc = fail(IPGC_EBADCSR, "decreasing rowptr or a column id outside [0, n)");
-                break;
-            }
-        }
-        const int32_t zero3[3] = {0, 0, 0}, src32 = (int32_t)source, dist0 = 0, unset = -1;
-        std::vector<int32_t> cnt(kMaxRoundBlocks, 0);
-        cnt[0] = 1;
-        if (hipMemsetAsync(out_dist, 0xff, sizeof(int32_t) * n, s) != hipSuccess ||
-            hipMemcpyAsync(out_dist + source, &dist0, sizeof(int32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(seg0.p, &src32, sizeof(int32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(cnt0.p, cnt.data(), sizeof(int32_t) * kMaxRoundBlocks, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemsetAsync(cnt1.p, 0, sizeof(int32_t) * kMaxRoundBlocks, s) != hipSuccess ||
-            hipMemcpyAsync(ovfc.p, zero3, sizeof zero3, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(lv.p, &unset, sizeof(int32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemsetAsync(bar.p, 0, sizeof(Barrier), s) != hipSuccess) {
-            rc = fail(IPGC_EHIP, "BFS set-up failed");
-            break;
-        }
-        d.rowptr = rowptr;
-        d.colidx = colidx;
-        d.dist = out_dist;
-        d.seg[0] = seg0.p;
-        d.seg[1] = seg1.p;
-        d.seg_cnt[0] = cnt0.p;
-        d.seg_cnt[1] = cnt1.p;
-        d.ovf[0] = ovf0.p;
-        d.ovf[1] = ovf1.p;
-        d.ovf_cnt = ovfc.p;
-        d.trace = tr.p;
-        d.trace_cap = n + 1;
-        d.n = n;
-        d.threshold = H;
-        d.levels = lv.p;
-        d.bar = bar.p;
-        if ((rc = barrier_limit_ticks(dev, P.barrier_ms, &d.bar_limit))) break;
-        void *args[] = {&d};
-        if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_bfs), dim3(grid), dim3(kBlock), args, 0, s) !=
-            hipSuccess) {
-            rc = fail(IPGC_EHIP, "BFS launch failed");
-            break;
-        }
-        int32_t levels = -1;
-        if (hipMemcpyAsync(&levels, lv.p, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess) {
-            rc = fail(IPGC_EHIP, "BFS read-back failed");
-            break;
-        }
-        if (levels < 0) {
-            rc = fail(IPGC_EHIP, "a grid-barrier wait exceeded %d ms: not every workgroup of the cooperative launch ran "
-                      "(%d workgroups)", P.barrier_ms, grid);
-            break;
-        }
-        if (trace) {
-            const int64_t k = std::min<int64_t>(trace->capacity, levels);
-            if (k > 0 && trace->wl_size &&
-                hipMemcpy(trace->wl_size, tr.p, sizeof(int32_t) * k, hipMemcpyDeviceToHost) != hipSuccess) {
-                rc = fail(IPGC_EHIP, "BFS trace read-back failed");
-                break;
-            }
-            if (k > 0 && trace->topology && trace->wl_size)
-                for (int64_t i = 0; i < k; ++i) trace->topology[i] = (int8_t)((int64_t)trace->wl_size[i] > H);
-            trace->recorded = k;
-        }
-        *out_levels = levels;
-    } while (false);
-    if (rc == IPGC_OK) g_err[0] = 0;
-    return rc;
+    d.rowptr = rowptr;
+    d.colidx = colidx;
+    d.dist = out_dist;
+    d.seg[0] = w.seg0.p;
+    d.seg[1] = w.seg1.p;
+    d.seg_cnt[0] = w.cnt0.p;
+    d.seg_cnt[1] = w.cnt1.p;
+    d.ovf[0] = w.ovf0.p;
+    d.ovf[1] = w.ovf1.p;
+    d.hub = w.hub.p;
+    d.trace = w.tr.p;
+    d.trace_cap = n + 1;
+    d.n = n;
+    d.m = m;
+    d.threshold = H;
+    d.source = (int32_t)source;
+    d.cap = cap;
+    d.ctl = w.ctl.p;
+    d.bar = w.bar.p;
+    TRY(barrier_limit_ticks(dev, P.barrier_ms, &d.bar_limit));
+    TRY(clear(w.ctl.p, sizeof(BfsCtl), s));
+    TRY(clear(w.bar.p, sizeof(Barrier), s));
+    // the search reads no row when the checks fail, so the host waits once, at the end
+    const int64_t work = n + (P.check_ids ? m / 8 : 0);
+    k_bfs_prep<<<(int)std::min<int64_t>(4096, (work + 255) / 256), 256, 0, s>>>(d, P.check_ids ? 1 : 0);
+    HIP_TRY(hipGetLastError());
+    void *args[] = {&d};
+    HIP_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_bfs), dim3(grid), dim3(kBlock), args, 0, s));
+    HIP_TRY(hipMemcpyAsync(w.host_ctl, w.ctl.p, sizeof(BfsCtl), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    const BfsCtl h = *w.host_ctl;
+    if (h.bad_ends) return fail(IPGC_EBADCSR, "rowptr[0] != 0 or rowptr[n] != m");
+    if (h.bad) return fail(IPGC_EBADCSR, "decreasing rowptr or a column id outside [0, n)");
+    if (!h.done)
+        return fail(IPGC_EHIP, "a grid-barrier wait exceeded %d ms: not every workgroup of the cooperative launch ran "
+                    "(%d workgroups)", P.barrier_ms, grid);
+    if (trace) {
+        const int64_t k = std::min<int64_t>(trace->capacity, h.levels);
+        if (k > 0 && trace->wl_size)
+            HIP_TRY(hipMemcpy(trace->wl_size, w.tr.p, sizeof(int32_t) * k, hipMemcpyDeviceToHost));
+        if (k > 0 && trace->topology && trace->wl_size)
+            for (int64_t i = 0; i < k; ++i) trace->topology[i] = (int8_t)((int64_t)trace->wl_size[i] > H);
+        trace->recorded = k;
+    }
+    *out_levels = h.levels;
+    g_err[0] = 0;
+    return IPGC_OK;
+}
+
+}  // namespace bfs
+}  // namespace ipgc
+
+extern "C" int ipgc_bfs(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m, int64_t source, int mode,
+                        const ipgc_options *options, void *stream, int32_t *out_dist, int32_t *out_levels,
+                        ipgc_trace *trace) {
+    IPGC_GUARD(ipgc::bfs::bfs_impl(rowptr, colidx, n, m, source, mode, options, (hipStream_t)stream, out_dist, out_levels,
+                                   trace));
 }

@@ -82,3 +82,33 @@ def test_bfs_errors():
         ip.bfs(rp, bad, 0)
     assert e.value.code == -3
     check(g, 2, "hybrid")
+
+
+# Rows of more than 2048 entries are expanded by the whole grid in chunks of 256 entries, up to 1024
+# such rows staged at a time: row lengths around both edges, and a level with 1100 of them.
+@pytest.mark.parametrize("g", [gg.star(2048, 0), gg.star(2049, 0), gg.star(2304, 7), gg.star(2305, 2305),
+                               gg.complete_bipartite(1100, 2100)], ids=lambda g: g.name)
+def test_bfs_rows_spread_over_the_grid(g):
+    for source in sorted({0, g.n // 2, g.n - 1}):
+        for mode in MODES:
+            check(g, source, mode, workgroups=3)
+
+
+def test_bfs_checks_come_before_any_row_is_read():
+    """Bad row pointers and ids anywhere in the entry array, also in entries past the last full stride."""
+    import paper_1912_01478_amd as ip
+    g = gg.erdos_renyi(5003, 7.0, gg.key(911, 0))
+    rp, ci = torch.from_numpy(g.rowptr).cuda(), torch.from_numpy(g.colidx).cuda()
+    for at, value in ((0, -1), (g.m // 2, g.n), (g.m - 1, 2**31 - 1)):
+        bad = ci.clone()
+        bad[at] = value
+        with pytest.raises(ip.IpgcError) as e:
+            ip.bfs(rp, bad, 0)
+        assert e.value.code == -3
+    for at, value in ((0, 1), (g.n, g.m - 1), (g.n // 2, -4), (g.n // 2, g.m + 1)):
+        bad = rp.clone()
+        bad[at] = value
+        with pytest.raises(ip.IpgcError) as e:
+            ip.bfs(bad, ci, 0)
+        assert e.value.code == -3
+    check(g, 0, "hybrid")
