@@ -37,6 +37,7 @@
 #include <vector>
 
 #include "ipgc.h"
+#include "ipgc_core.hpp"
 #include "ipgc_device.hpp"
 #include "ipgc_host.hpp"
 
@@ -111,6 +112,8 @@ struct Workspace {
     DBuf<uint64_t> ticks;
     DBuf<Barrier> bar;
     DBuf<Counters> ctb;
+    DBuf<uint64_t> core_adj;    // k_core_rounds: bit matrix and nodes
+    DBuf<CoreNode> core_node;
     DBuf<int32_t> sorted_rows;  // IPGC_VALIDATE_FULL: every row sorted (m entries)
     Counters *ct = nullptr;       // ctb.p
     Counters *host_ct = nullptr;  // pinned (or &host_local for a carved workspace)
@@ -154,8 +157,17 @@ struct Workspace {
         return IPGC_OK;
     }
 
+    // What a call can do without (132 KiB + 32 KiB): the last rounds then run in k_rounds.
+    template <class Fn>
+    int plan_core(Fn &&f) {
+        TRY(f(core_adj, (int64_t)kCore * kCoreWords));
+        TRY(f(core_node, kCore));
+        return IPGC_OK;
+    }
+
     int reserve(int64_t n, int64_t m, int grid, int prep_grid, int hub_min, bool full, bool split = false) {
         TRY(plan(n, m, grid, prep_grid, hub_min, full, split, [](auto &b, int64_t c) { return b.reserve(c); }));
+        if (!borrowed) TRY(plan_core([](auto &b, int64_t c) { return b.reserve(c); }));
         ct = ctb.p;
         if (!host_ct) HIP_TRY(hipHostMalloc(&host_ct, sizeof(Counters), hipHostMallocDefault));
         return IPGC_OK;
@@ -167,7 +179,7 @@ struct Workspace {
     int carve(unsigned char *base, size_t size, int64_t n, int64_t m, int grid, int prep_grid, int hub_min, bool full,
               size_t *used) {
         size_t off = 0;
-        TRY(plan(n, m, grid, prep_grid, hub_min, full, false, [&](auto &b, int64_t c) {
+        auto place = [&](auto &b, int64_t c) {
             using T = std::remove_reference_t<decltype(*b.p)>;
             off = (off + 255) & ~(size_t)255;
             const size_t bytes = sizeof(T) * (size_t)c;
@@ -175,11 +187,13 @@ struct Workspace {
             else b.release();
             off += bytes;
             return IPGC_OK;
-        }));
+        };
+        TRY(plan(n, m, grid, prep_grid, hub_min, full, false, place));
         *used = off;
         if (off > size)
             return fail(IPGC_ETOOBIG, "this graph needs %llu bytes of scratch; the static scratch holds %llu",
                         (unsigned long long)off, (unsigned long long)size);
+        TRY(plan_core(place));  // if it fits too (core_adj.p and core_node.p null if not)
         ct = ctb.p;
         host_ct = &host_local;
         borrowed = true;
@@ -194,6 +208,7 @@ struct Workspace {
         F.release(); mask.release(); pend.release(); ticks.release(); bar.release(); growptr.release(); node_off.release(); edge_off.release();
         gbase.release(); gidx.release(); grounds.release(); ctb.release(); sorted_rows.release();
         gthr.release(); gleft.release(); trace_topo.release(); gsplit.release();
+        core_adj.release(); core_node.release();
         if (host_ct && !borrowed) (void)hipHostFree(host_ct);
         for (hipEvent_t e : events) (void)hipEventDestroy(e);
         *this = Workspace();
@@ -489,9 +504,23 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
     d.sorted = P.check_ids && !ws.host_ct->unsorted;
     if (P.full) TRY(check_full(ws, s, d, n, m));
 
+    // The last rounds on one workgroup: not in the sweeps of TOPOLOGY (every round a sweep is what that
+    // mode asks for), without a worklist (REBUILD), or in place (racy).
+    const CoreMem cm{ws.core_adj.p, ws.core_node.p, ws.static_list.p};
+    const bool core = coop > 0 && P.mode != IPGC_MODE_TOPOLOGY && !d.discard && !d.racy && cm.adj && cm.node;
+    auto core_launch = [&](const auto &dv) -> int {
+        using DV = std::decay_t<decltype(dv)>;
+        k_core_rank<<<kCoreRankGroups, kCore, 0, s>>>(dv, cm);
+        k_core_build<<<(int)std::min<int64_t>(kCore, n), kCore, 0, s>>>(dv, cm);
+        k_core_rounds<DV><<<1, kCore, 0, s>>>(dv, cm);
+        HIP_TRY(hipGetLastError());
+        return IPGC_OK;
+    };
+
     // Rounds: at most n (the worklist shrinks every round), plus the start of the one that finds it empty.
     if (coop > 0) {
         int32_t first = 1, last = (int32_t)std::min<int64_t>(n + 1, INT32_MAX - 2);
+        if constexpr (!D::kSplit) d.core_max = core ? kCore : 0;
         void *args[] = {&d, &first, &last};
         TRY(pf.begin(kKindRounds));
         // one graph whose nodes all pull: round 1 needs no state reads, in a launch of its own so
@@ -505,6 +534,9 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
         }
         HIP_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_rounds<D>), dim3(grid),
                                            dim3(kRoundBlock), args, 0, s));
+        if constexpr (!D::kSplit) {
+            if (core) TRY(core_launch(d));
+        }
         TRY(pf.end(kKindRounds));
         TRY(read_counters(ws, s));
         if constexpr (D::kSplit) {
@@ -517,12 +549,14 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
                 d2.threshold = INT64_MAX;
                 d2.gleft = nullptr;
                 d2.gthr = nullptr;
+                d2.core_max = core ? kCore : 0;
                 int32_t first2 = ws.host_ct->resume_round;
                 void *args2[] = {&d2, &first2, &last};
                 TRY(clear(ws.bar.p, sizeof(Barrier), s));
                 TRY(pf.begin(kKindRounds));
                 HIP_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_rounds<DevT<Off, false>>),
                                                    dim3(grid), dim3(kRoundBlock), args2, 0, s));
+                if (core) TRY(core_launch(d2));
                 TRY(pf.end(kKindRounds));
                 TRY(read_counters(ws, s));
             }

@@ -146,6 +146,9 @@ struct Counters {
     int32_t split_data;               // each kind in the current round (written by its assign launch)
     int32_t resume_round;             // per-graph schedules: the round from which every graph runs data-driven,
                                       // left by the per-graph round kernel to the plain one (0: none)
+    int32_t tail_round;               // round from which the rounds go on in k_core_rounds (0: none left to it)
+    int32_t tail_writers;             // workgroups that wrote that round's worklist
+    int32_t tail_nodes;               // its nodes
     int64_t ends[2];
 };
 
@@ -216,6 +219,7 @@ struct DevT {
     int32_t light_pull;      // kPushAll, kPullLight or kPullOnly: how class L learns its neighbours' colors
     int32_t racy;            // in-place mode: losers uncolor at once, L assigns avoid in-flight tentatives
     int32_t discard;         // topology-driven rounds keep no worklist; it is rebuilt when data rounds start
+    int32_t core_max;        // worklists of at most this many nodes are left to k_core_rounds (0: none)
     int32_t tail_groups;     // workgroups that stay in the round loop for small data-driven rounds (0: all)
     uint64_t bar_limit;      // wall-clock ticks a grid-barrier wait may last
     const int32_t *gthr;     // a batch with per-graph schedules: H_g per graph (null: one decision per round)
@@ -2300,6 +2304,13 @@ __global__ __launch_bounds__(kRoundBlock) void k_rounds(D d, int32_t first, int3
                 if (r > 1) in = graph_round(d, r, pre, sp, &two);
                 if (blockIdx.x == 0 && threadIdx.x == 0 && r - 1 < d.topo_cap) d.trace_topo[r - 1] = sp.topo;
             }
+        }
+        if (r > 1 && in.total > 0 && in.total <= d.core_max) {  // the rounds from here on run on one workgroup
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                d.ct->tail_round = r;
+                d.ct->tail_writers = writers;
+            }
+            break;
         }
         if (discarded && !in.topo && in.total > 0) {
             rebuild_step(d, r & 1, G);
