@@ -126,8 +126,8 @@ typedef struct ipgc_options {
     int32_t validate;          /* IPGC_VALIDATE_* */
     int32_t flags;             /* IPGC_FLAG_* */
     ipgc_profile *profile;     /* optional per-kernel timing and work counts (NULL: none) */
-    int32_t workgroups;        /* workgroups of the round kernels (0: one per 4096 nodes, at most what
-                                  the device keeps resident at once; larger values are clamped to that) */
+    int32_t workgroups;        /* workgroups of the round kernels (0: one per 1024 nodes or 3072 entries,
+                                  whichever is more, at most what the device keeps resident at once; larger values are clamped to that) */
     int32_t tail_workgroups;   /* once a data-driven round has at most 32 * tail_workgroups active nodes,
                                   only this many workgroups stay in the cooperative round loop (cheaper
                                   grid barriers for the long tail of small rounds; 0: default, negative:
@@ -210,7 +210,8 @@ int ipgc_color_graph_ex(const int32_t *csr_rowptr, const int32_t *csr_colidx, in
  *
  * The workspace of a graph takes about 46 bytes per node, 5 bytes per CSR
  * entry (9 with IPGC_VALIDATE_FULL) and 25 KiB per round workgroup (one per
- * 4096 nodes, at most 256 on MI355X): 256 MiB hold, for example, every graph
+ * 1024 nodes or 3072 entries, at most 256 on MI355X; one per 4096 nodes where more
+ * would not fit): 256 MiB hold, for example, every graph
  * of up to 10^6 nodes and 32 * 10^6 entries.  A graph that does not fit
  * returns IPGC_ETOOBIG before any device work.  options->profile must be NULL
  * (IPGC_EINVAL): a profile needs events and a tick buffer.

@@ -369,11 +369,21 @@ Workspace &workspace(int dev) {
     return g_ws[dev];
 }
 
-// Round grid: enough workgroups for the first round, at most what is co-resident.
-int round_grid(Workspace &ws, int dev, const Params &P, int64_t n, int *grid, int *coop) {
+// Round grid: a workgroup per kRoundBlock nodes or kGroupEntries row entries, whichever asks for more, at
+// most what is co-resident.  A round's nodes are chains of dependent loads, so spreading them wider shortens
+// every round until the grid barrier (3 us with 64 workgroups, 5 us with 256) costs as much.  Measured
+// against a workgroup per 4 * kRoundBlock nodes: R-MAT of 65 536 nodes and 1.8e6 entries 2990 us with 16
+// workgroups, 2276 with 64, 2074 with 256; R-MAT of 8192 and 2.0e5 entries 1157 us with 2, 854 with 64, 888
+// with 192; uniform, 10^4 nodes and 8.0e4 entries, 330 us with 3, 271 with 32, 295 with 256; road-like, 10^5
+// nodes and 2.4e5 entries, 292 us with 25, 279 with 96, 296 with 256.
+constexpr int64_t kGroupEntries = 3072;
+
+int round_grid(Workspace &ws, int dev, const Params &P, int64_t n, int64_t m, bool narrow, int *grid, int *coop) {
     *coop = 0;
     if (!P.stepped) TRY(cooperative_capacity(ws, dev, coop));
-    const int64_t want = P.workgroups > 0 ? P.workgroups : (n + 4 * kRoundBlock - 1) / (4 * kRoundBlock);
+    int64_t want = P.workgroups;
+    if (want == 0 && (P.stepped || narrow)) want = (n + 4 * kRoundBlock - 1) / (4 * kRoundBlock);
+    else if (want == 0) want = std::max((n + kRoundBlock - 1) / kRoundBlock, (m + kGroupEntries - 1) / kGroupEntries);
     *grid = (int)std::max<int64_t>(1, std::min<int64_t>(want, *coop > 0 ? *coop : kMaxRoundBlocks));
     return IPGC_OK;
 }
@@ -654,7 +664,7 @@ int color_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t 
 
     // rowptr[0] == 0 and rowptr[n] == m are checked by k_init, before any row is read
     int grid = 1, coop = 0;
-    TRY(round_grid(ws, dev, P, n, &grid, &coop));
+    TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
     DevT<int32_t> d{};
     d.rowptr = rowptr;
     d.colidx = colidx;
@@ -714,7 +724,7 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
     HIP_TRY(hipGetLastError());
 
     int grid = 1, coop = 0;
-    TRY(round_grid(ws, dev, P, n, &grid, &coop));
+    TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
     auto setup = [&](auto &d) {
         d.rowptr = ws.growptr.p;
         d.colidx = colidx_packed;
@@ -828,12 +838,18 @@ int color_noalloc_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, 
     TRY(static_scratch(dev, &base));
     Workspace &ws = g_static_ws[dev];
     int grid = 1, coop = 0;
-    TRY(round_grid(ws, dev, P, n, &grid, &coop));
     int64_t span = 0;
     int prep_grid = 0;
     prep_layout(n, &span, &prep_grid);
     size_t used = 0;
-    TRY(ws.carve(base, kStaticScratchBytes, n, m, grid, prep_grid, P.hub_min, P.full, &used));
+    // every workgroup takes 25 KiB of scratch: a graph near the scratch's end gets fewer
+    TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
+    int rc = ws.carve(base, kStaticScratchBytes, n, m, grid, prep_grid, P.hub_min, P.full, &used);
+    if (rc == IPGC_ETOOBIG) {
+        TRY(round_grid(ws, dev, P, n, m, true, &grid, &coop));
+        rc = ws.carve(base, kStaticScratchBytes, n, m, grid, prep_grid, P.hub_min, P.full, &used);
+    }
+    TRY(rc);
 
     DevT<int32_t> d{};
     d.rowptr = rowptr;
