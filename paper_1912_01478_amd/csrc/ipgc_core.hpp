@@ -18,7 +18,7 @@ namespace ipgc {
 constexpr int kCore = 1024;                // nodes: a thread each
 constexpr int kCoreWords = kCore / 64;     // words of a matrix row
 constexpr int kCoreStride = kCore + 1;     // words per column of the matrix: rows and columns both free of bank conflicts
-constexpr int kCoreBuckets = 64;           // tentative colors modulo 64
+constexpr int kCoreBuckets = 128;          // tentative colors modulo 128
 
 // What the core needs of one uncolored node (global memory, by rank: ascending id).
 struct CoreNode {
@@ -38,148 +38,227 @@ struct CoreMem {
 
 struct CoreShared {
     uint64_t adj[kCoreWords * kCoreStride];        // word w of row i at [w * kCoreStride + i]; symmetric
-    uint64_t bucket[kCoreWords * kCoreBuckets];    // [w][h]: uncolored nodes of word w with tentative color h modulo 64
+    uint64_t bucket[kCoreWords * kCoreBuckets];    // [w][h]: uncolored nodes of word w with tentative color h modulo 128
     uint64_t won[kCoreWords];                      // nodes that commit in this round
+    uint64_t done[kCoreWords];                     // nodes committed in earlier rounds (their colors stay in t)
     int32_t t[kCore];
-    uint16_t win[kCore];                           // the same as a list
+    int cnt[kCoreWords];
     int nwin;
     unsigned long long wdeg;                       // degree sum of the nodes that commit
 };
 static_assert(sizeof(CoreShared) <= 160 * 1024, "one workgroup's shared memory");
 
-// A thread's node: its state, and the colors its committed neighbours hold from base + 1 on.
+// A thread's node: its state, and which colors from base + 1 on its committed neighbours hold.
 struct CoreState {
-    uint64_t lo = 0, hi = 0;   // bit k: color base + 1 + k
+    uint64_t lo = 0, hi = 0;   // bit k: color base + 1 + k (hi: base + 65 + k)
     int32_t v = -1, base = 0, t = 0, deg = 0;
+    int32_t rank = 0;
 };
 
-// Committed neighbour with color x: into the window, or (a color past it) into the node's byte map,
-// which this thread alone uses now.  Maps hold colors up to d + 1; a larger one never matters.
-template <class D>
-__device__ __forceinline__ void core_forbid(const D &d, CoreState &s, int32_t x) {
-    const int32_t k = x - 1 - s.base;
-    if (k < 0) return;
-    if (k < 64) s.lo |= 1ull << k;
-    else if (k < 128) s.hi |= 1ull << (k - 64);
-    else {
-        const MapRef fm = map_of(d, s.v, d.fshift(s.v));
-        if ((uint32_t)x <= fm.size) d.F[fm.pos + x - 1] = 1;
-    }
+// A neighbour has committed color x.  Colors past the window are found again when it moves on.
+__device__ __forceinline__ void core_forbid(CoreState &s, int32_t x) {
+    const uint32_t k = (uint32_t)(x - 1 - s.base);
+    const uint64_t bit = 1ull << (k & 63);
+    if (k < 64) s.lo |= bit;
+    else if (k < 128) s.hi |= bit;
 }
 
-// The smallest color not forbidden.  A full window moves on by 128 colors (all above 64, so the byte
-// map holds what is known of them).
+// What a node's byte map says of the 64 colors from x on, all above 64 (bit k: color x + k): the state that
+// the rounds before the core left.
 template <class D>
-__device__ __forceinline__ int32_t core_first_free(const D &d, CoreState &s) {
-    while ((s.lo & s.hi) == ~0ull) {
-        s.base += 128;
-        s.lo = s.hi = 0;
+struct CoreMaps {
+    const D &d;
+    __device__ __forceinline__ uint64_t taken(const CoreState &s, int32_t x) const {
         const MapRef fm = map_of(d, s.v, d.fshift(s.v));
-        for (int k = 0; k < 128 && (uint32_t)(s.base + k) < fm.size; ++k) {
-            if (!d.F[fm.pos + s.base + k]) continue;
-            if (k < 64) s.lo |= 1ull << k;
-            else s.hi |= 1ull << (k - 64);
+        uint64_t m = 0;
+        for (int k = 0; k < 64 && (uint32_t)(x - 1 + k) < fm.size; ++k) m |= (uint64_t)(d.F[fm.pos + x - 1 + k] & 1) << k;
+        return m;
+    }
+};
+
+// Workgroup barrier for shared memory alone: stores to global memory stay in flight (nothing in the core
+// reads them back), where __syncthreads would wait a microsecond for each round's colors to be written.
+__device__ __forceinline__ void core_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The smallest color not forbidden, after round r.  A full first word moves the window on by 64 colors.  No
+// color above r has been committed yet, so the word that comes in is empty unless the node is more than
+// 64 colors behind the rounds; then it holds the colors taken before the core (by round r0 - 1) and
+// those of the node's neighbours that the core has committed.
+template <class Far>
+__device__ __forceinline__ int32_t core_first_free(const Far &far, const CoreShared &sh, CoreState &s, int32_t r0, int32_t r) {
+    while (s.lo == ~0ull) {
+        s.base += 64;
+        s.lo = s.hi;
+        s.hi = 0;
+        if (s.base + 64 >= r) continue;
+        if (s.base + 64 < r0) s.hi = far.taken(s, s.base + 65);
+        for (int w = 0; w < kCoreWords; ++w) {
+            uint64_t x = sh.adj[w * kCoreStride + s.rank] & (sh.done[w] | sh.won[w]);
+            for (; x; x &= x - 1) core_forbid(s, sh.t[w * 64 + __ffsll((unsigned long long)x) - 1]);
         }
     }
-    return s.base + (s.lo != ~0ull ? __ffsll((unsigned long long)~s.lo) : 64 + __ffsll((unsigned long long)~s.hi));
+    return s.base + __ffsll((unsigned long long)~s.lo);
 }
 
-// Rounds r, r + 1, ... until every node of the core is colored, by the whole workgroup (kCore threads;
+// The nodes still uncolored move to the first threads (nact of them, at most half of `span`), in rank order,
+// so that the other wavefronts have nothing left to do.  Called by the whole workgroup.
+__device__ __forceinline__ void core_compact(CoreShared &sh, CoreState &s, bool act, int nact) {
+    const int i = threadIdx.x, w = i / kWave, lane = lane_id();
+    const uint64_t am = __ballot(act);
+    if (lane == 0) sh.cnt[w] = __popcll(am);
+    core_sync();
+    int at = __popcll(am & lanes_below());
+    for (int q = 0; q < kCoreWords; ++q) at += q < w ? sh.cnt[q] : 0;
+    uint64_t *stage = sh.bucket;  // all zero between rounds, at most kCore / 2 nodes
+    static_assert(kCoreWords * kCoreBuckets >= kCore / 2, "staging area");
+    const uint64_t in[5] = {s.lo, s.hi, (uint64_t)(uint32_t)s.v << 32 | (uint32_t)s.deg,
+                            (uint64_t)(uint32_t)s.t << 32 | (uint32_t)s.base, (uint64_t)(uint32_t)s.rank};
+    uint64_t out[5];
+#pragma unroll
+    for (int f = 0; f < 5; ++f) {
+        if (act) stage[at] = in[f];
+        core_sync();
+        out[f] = i < nact ? stage[i] : 0;
+        core_sync();
+    }
+    if (i < kCore / 2) stage[i] = 0;
+    core_sync();
+    s.lo = out[0];
+    s.hi = out[1];
+    s.v = i < nact ? (int32_t)(out[2] >> 32) : -1;
+    s.deg = (int32_t)out[2];
+    s.t = (int32_t)(out[3] >> 32);
+    s.base = (int32_t)out[3];
+    s.rank = (int32_t)out[4];
+}
+
+// Rounds r0, r0 + 1, ... until every node of the core is colored, by the whole workgroup (kCore threads;
 // thread i holds the node of rank i, s.v < 0 for none).  commit(s, round) stores a node's color;
 // record(round, nodes, degree sum) is called by thread 0 at the start of every round with the uncolored
 // nodes.  Returns the number of the last round; *sum_nodes: the uncolored nodes summed over the rounds.
 //
 // A node loses iff a smaller uncolored neighbour has the same tentative color.  Candidates are the
-// neighbours whose color agrees modulo 64, found word by word from the bucket sets; each is compared
-// exactly.  Losers then learn the colors committed by their neighbours: from the list of winners if
-// it is short, else from their matrix row against the winners' set.
-template <class D, class Commit, class Record>
-__device__ __forceinline__ int32_t core_rounds(const D &d, CoreShared &sh, CoreState s, int32_t r, int nact, int64_t degsum,
-                                               int64_t *sum_nodes, Commit &&commit, Record &&record) {
-    const int i = threadIdx.x, w = i / kWave, lane = lane_id(), h0 = i;
+// neighbours whose color agrees modulo 128, found word by word from the bucket sets, and compared exactly.
+// Losers then learn the colors committed by their neighbours, from their matrix row against the winners' set;
+// the winners and their colors are the same for the whole wavefront, so they come from scalar registers.
+template <class Far, class Commit, class Record>
+__device__ __forceinline__ int32_t core_rounds(const Far &far, CoreShared &sh, CoreState s, int32_t r0, int nact,
+                                               int64_t degsum, int64_t *sum_nodes, Commit &&commit, Record &&record) {
+    const int i = threadIdx.x, w = i / kWave, lane = lane_id();
     bool act = s.v >= 0;
-    if (act) s.t = core_first_free(d, s);
+    int span = kCore;  // threads that may hold a node
+    int32_t r = r0;
+    s.rank = i;
+    if (i < kCoreWords) sh.done[i] = sh.won[i] = 0;
+    for (int k = i; k < kCoreWords * kCoreBuckets; k += kCore) sh.bucket[k] = 0;
+    core_sync();
+    if (act) s.t = core_first_free(far, sh, s, r0, r - 1);
     *sum_nodes = 0;
     for (; nact > 0; ++r) {
         if (i == 0) record(r, nact, degsum);
         *sum_nodes += nact;
-        sh.bucket[h0] = 0;  // kCoreWords * kCoreBuckets words, one per thread
-        if (act) sh.t[i] = s.t;
-        __syncthreads();
+        if (span > kWave && nact <= span / 2) {  // the same for the whole workgroup
+            core_compact(sh, s, act, nact);
+            act = s.v >= 0;
+            while (span > kWave && nact <= span / 2) span /= 2;
+        }
+        const int rw = s.rank / 64, h = s.t & (kCoreBuckets - 1);
+        const uint64_t rbit = 1ull << (s.rank & 63);
+        unsigned long long *const mine = (unsigned long long *)&sh.bucket[rw * kCoreBuckets + h];
+        if (act) sh.t[s.rank] = s.t;
+        const uint64_t am = __ballot(act);
+        if (am) {
+            if (span == kCore) {  // a wavefront's nodes share a word: most of them go in at once
+                const int lead = __ffsll((unsigned long long)am) - 1;
+                const int hl = __builtin_amdgcn_readlane(h, lead);
+                const uint64_t same = __ballot(act && h == hl);
+                if (lane == lead) atomicOr(mine, (unsigned long long)same);
+                if (act && h != hl) atomicOr(mine, (unsigned long long)rbit);
+            } else if (act) {
+                atomicOr(mine, (unsigned long long)rbit);
+            }
+        }
+        core_sync();  // everyone has left the previous round
+        if (i < kCoreWords) {
+            sh.done[i] |= sh.won[i];
+            sh.won[i] = 0;
+        }
         if (i == 0) {
             sh.nwin = 0;
             sh.wdeg = 0;
         }
-        const int h = s.t & (kCoreBuckets - 1);
-        const uint64_t am = __ballot(act);
-        if (am) {  // the leading lane's color goes in at once (late in the run nearly all agree)
-            const int lead = __ffsll((unsigned long long)am) - 1;
-            const int hl = __shfl(h, lead);
-            const uint64_t same = __ballot(act && h == hl);
-            unsigned long long *col = (unsigned long long *)&sh.bucket[w * kCoreBuckets];
-            if (lane == lead) atomicOr(&col[hl], (unsigned long long)same);
-            if (act && h != hl) atomicOr(&col[h], 1ull << lane);
-        }
-        __syncthreads();
         bool lose = false;
         if (act) {
-            for (int w0 = 0; w0 <= w && !lose; w0 += 4) {
+            for (int w0 = 0; w0 <= rw && !lose; w0 += 4) {
                 uint64_t x[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {  // the four words' loads are in flight together
                     const int ww = w0 + q;
-                    x[q] = ww <= w ? sh.adj[ww * kCoreStride + i] & sh.bucket[ww * kCoreBuckets + h] : 0;
-                    if (ww == w) x[q] &= lanes_below();
+                    x[q] = ww <= rw ? sh.adj[ww * kCoreStride + s.rank] & sh.bucket[ww * kCoreBuckets + h] : 0;
+                    if (ww == rw) x[q] &= rbit - 1;
                 }
+                while ((x[0] | x[1] | x[2] | x[3]) && !lose) {
+                    const int q = x[0] ? 0 : x[1] ? 1 : x[2] ? 2 : 3;
+                    const uint64_t y = x[0] ? x[0] : x[1] ? x[1] : x[2] ? x[2] : x[3];
+                    lose = sh.t[(w0 + q) * 64 + __ffsll((unsigned long long)y) - 1] == s.t;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    while (x[q] && !lose) {
-                        lose = sh.t[(w0 + q) * 64 + __ffsll((unsigned long long)x[q]) - 1] == s.t;
-                        x[q] &= x[q] - 1;
-                    }
+                    for (int p = 0; p < 4; ++p)
+                        if (p == q) x[p] &= x[p] - 1;
                 }
             }
         }
+        core_sync();
         const bool win = act && !lose;
         const uint64_t wm = __ballot(win);
-        if (lane == 0) sh.won[w] = wm;
+        if (act) *mine = 0;
         if (wm) {
-            int at = 0;
-            const int64_t wd = wave_sum(win ? s.deg : 0);
-            if (lane == 0) {
-                at = atomicAdd(&sh.nwin, (int)__popcll(wm));
-                atomicAdd(&sh.wdeg, (unsigned long long)wd);
-            }
-            at = __shfl(at, 0);
+            if (lane == 0) atomicAdd(&sh.nwin, (int)__popcll(wm));
             if (win) {
-                sh.win[at + __popcll(wm & lanes_below())] = (uint16_t)i;
+                atomicOr((unsigned long long *)&sh.won[rw], (unsigned long long)rbit);
+                atomicAdd(&sh.wdeg, (unsigned long long)s.deg);
                 commit(s, r);
             }
         }
-        __syncthreads();
-        const int nwin = sh.nwin;
+        core_sync();
+        nact -= sh.nwin;
         degsum -= (int64_t)sh.wdeg;
-        if (act && lose) {
-            if (nwin <= kCoreWords) {
-                for (int k = 0; k < nwin; ++k) {
-                    const int j = sh.win[k];
-                    if (sh.adj[(j >> 6) * kCoreStride + i] >> (j & 63) & 1) core_forbid(d, s, sh.t[j]);
+        act = act && lose;
+        if (__ballot(act)) {
+            const uint64_t wv = sh.won[lane & (kCoreWords - 1)];
+            uint32_t nz = (uint32_t)__ballot(wv != 0) & ((1u << kCoreWords) - 1);  // words with winners
+            while (nz) {  // two words at a time, their loads in flight together
+                int at[2], tq[2];
+                uint64_t m[2], a[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    at[q] = nz ? __ffs(nz) - 1 : 0;
+                    m[q] = nz ? (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(wv >> 32), at[q]) << 32 |
+                                    (uint32_t)__builtin_amdgcn_readlane((int)wv, at[q])
+                              : 0;
+                    nz &= nz - 1;
+                    a[q] = act ? sh.adj[at[q] * kCoreStride + s.rank] & m[q] : 0;
+                    tq[q] = sh.t[at[q] * 64 + lane];
                 }
-            } else {
-                for (int ww = 0; ww < kCoreWords; ++ww) {
-                    uint64_t x = sh.adj[ww * kCoreStride + i] & sh.won[ww];
-                    while (x) {
-                        core_forbid(d, s, sh.t[ww * 64 + __ffsll((unsigned long long)x) - 1]);
-                        x &= x - 1;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (!__ballot(a[q] != 0)) continue;
+                    if (__popcll(m[q]) <= 8) {
+                        for (uint64_t y = m[q]; y; y &= y - 1) {
+                            const int b = __ffsll((unsigned long long)y) - 1;
+                            if (a[q] >> b & 1) core_forbid(s, __builtin_amdgcn_readlane(tq[q], b));
+                        }
+                    } else {  // many winners: each lane takes its own neighbours among them
+                        for (uint64_t y = a[q]; y; y &= y - 1)
+                            core_forbid(s, sh.t[at[q] * 64 + __ffsll((unsigned long long)y) - 1]);
                     }
                 }
             }
-            s.t = core_first_free(d, s);
+            if (act) s.t = core_first_free(far, sh, s, r0, r);
         }
-        act = act && lose;
-        nact -= nwin;
-        // the next round's first barrier comes before nwin, wdeg, won and win are written again, and
-        // only losers write t before it
     }
     return r - 1;
 }
@@ -306,19 +385,26 @@ __global__ __launch_bounds__(kCore) void k_core_build(D d, CoreMem cm) {
     }
 }
 
-// Upper half of the matrix from its lower half, 64 x 64 bits at a time: column b of the block whose rows
-// a wavefront holds is one ballot.
+// The transpose of a 64 x 64 bit block (lane l holds row l), by exchanging half blocks of 32, 16, ... 1.
+__device__ __forceinline__ uint64_t core_transpose(uint64_t x) {
+    const int lane = lane_id();
+    uint64_t mask = 0x00000000FFFFFFFFull;  // the columns of the lower half of each block of 2 j
+#pragma unroll
+    for (int j = 32; j > 0; j >>= 1) {
+        const uint64_t y = (uint64_t)__shfl_xor((unsigned long long)x, j);
+        x = lane & j ? (x & ~mask) | (y >> j & mask) : (x & mask) | (y << j & ~mask);
+        mask ^= mask << (j >> 1);
+    }
+    return x;
+}
+
+// Upper half of the matrix from its lower half, 64 x 64 bits at a time.
 __device__ __forceinline__ void core_mirror(CoreShared &sh, int words) {
     const int lane = lane_id();
     for (int blk = threadIdx.x / kWave; blk < words * words; blk += kCore / kWave) {
         const int wi = blk / words, wj = blk % words;  // rows 64 wi.., columns 64 wj..
         if (wj > wi) continue;
-        const uint64_t x = sh.adj[wj * kCoreStride + wi * 64 + lane];
-        uint64_t y = 0;
-        for (int b = 0; b < 64; ++b) {
-            const uint64_t col = __ballot(x >> b & 1);
-            if (lane == b) y = col;
-        }
+        const uint64_t x = sh.adj[wj * kCoreStride + wi * 64 + lane], y = core_transpose(x);
         // row 64 wj + lane, word wi; a diagonal block keeps its lower half as well
         sh.adj[wi * kCoreStride + wj * 64 + lane] = wi == wj ? x | y : y;
     }
@@ -341,9 +427,16 @@ __global__ __launch_bounds__(kCore) void k_core_rounds(D d, CoreMem cm) {
         s.base = nd.t - 1;
         s.deg = nd.deg;
     }
-    for (int k = i; k < kCore * kCoreWords; k += kCore) {
-        const int row = k / kCoreWords, w = k % kCoreWords;
-        sh.adj[w * kCoreStride + row] = row < n ? cm.adj[k] : 0;
+    uint64_t word[kCoreWords];
+#pragma unroll
+    for (int q = 0; q < kCoreWords; ++q) {  // all loads in flight
+        const int k = q * kCore + i;
+        word[q] = k / kCoreWords < n ? cm.adj[k] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kCoreWords; ++q) {
+        const int k = q * kCore + i;
+        sh.adj[k % kCoreWords * kCoreStride + k / kCoreWords] = word[q];
     }
     if (i == 0) sh.wdeg = 0;
     __syncthreads();
@@ -355,7 +448,7 @@ __global__ __launch_bounds__(kCore) void k_core_rounds(D d, CoreMem cm) {
     __syncthreads();
     int64_t nodes = 0;
     const int32_t last = core_rounds(
-        d, sh, s, r0, n, degsum, &nodes,
+        CoreMaps<D>{d}, sh, s, r0, n, degsum, &nodes,
         [&](const CoreState &x, int32_t r) {
             d.c[x.v] = x.t;
             if (d.grounds) atomicMax(&d.grounds[d.gidx[x.v]], r);
