@@ -40,6 +40,7 @@
 #include "ipgc_core.hpp"
 #include "ipgc_device.hpp"
 #include "ipgc_host.hpp"
+#include "ipgc_small.hpp"
 
 namespace ipgc {
 
@@ -107,6 +108,7 @@ struct Workspace {
     DBuf<uint32_t> pend;
     DBuf<int64_t> growptr, node_off, edge_off;  // batches: union row starts, graph offsets
     DBuf<int32_t> gbase, gidx, grounds;         // batches: per-node graph base and index, rounds per graph
+    DBuf<int32_t> small;                        // batches: the graphs that k_small takes
     DBuf<int32_t> gthr, gleft, trace_topo;      // per-graph schedules: H_g, uncolored nodes per graph, trace
     DBuf<uint32_t> gsplit;                      // per-graph schedules, stepped launches: each graph's kind
     DBuf<uint64_t> ticks;
@@ -208,7 +210,7 @@ struct Workspace {
         F.release(); mask.release(); pend.release(); ticks.release(); bar.release(); growptr.release(); node_off.release(); edge_off.release();
         gbase.release(); gidx.release(); grounds.release(); ctb.release(); sorted_rows.release();
         gthr.release(); gleft.release(); trace_topo.release(); gsplit.release();
-        core_adj.release(); core_node.release();
+        core_adj.release(); core_node.release(); small.release();
         if (host_ct && !borrowed) (void)hipHostFree(host_ct);
         for (hipEvent_t e : events) (void)hipEventDestroy(e);
         *this = Workspace();
@@ -320,6 +322,8 @@ int parse_options(const ipgc_options *opt, int mode, Params *p) {
     p->check_ids = o.validate != IPGC_VALIDATE_NONE;
     p->stepped = (o.flags & IPGC_FLAG_STEPPED) != 0;
     p->threshold = o.threshold;
+    p->default_kernels = o.threshold <= 0 && !o.light_max_degree && !o.hub_min_degree && !o.flags && !o.workgroups &&
+                         !o.tail_workgroups && !o.barrier_timeout_ms;
     p->prof = o.profile;
     if (p->prof) {  // clear the out fields, keep the in fields
         ipgc_profile *pr = p->prof;
@@ -410,10 +414,80 @@ int check_full(Workspace &ws, hipStream_t s, const D &d, int64_t n, int64_t m) {
     return full_check_verdict(ws.host_ct->bad_full);
 }
 
+// Graphs that k_small takes: a call with the default kernel options and no profile, in the data-driven and
+// hybrid schedules (TOPOLOGY and REBUILD run the rounds they name; explicit options shape the round kernels).
+bool small_call(const Params &P) {
+    return (P.mode == IPGC_MODE_HYBRID || P.mode == IPGC_MODE_DATA) && P.default_kernels && !P.prof && !P.full;
+}
+
+// The entries up to which one workgroup is the faster one.
+constexpr int64_t kSmallEntries = 1 << 20;
+
+bool small_graph(int64_t n, int64_t m) { return n <= kSmallNodes && m <= kSmallEntries; }
+
+// Copies the per-round sizes out to the caller.
+int read_trace(Workspace &ws, hipStream_t s, ipgc_trace *trace, int32_t rounds, int64_t H) {
+    const int64_t k = std::min<int64_t>(trace->capacity, rounds);
+    if (k > 0 && trace->wl_size)
+        HIP_TRY(hipMemcpyAsync(trace->wl_size, ws.trace.p, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
+    if (k > 0 && trace->wl_degree)
+        HIP_TRY(hipMemcpyAsync(trace->wl_degree, ws.trace_deg.p, sizeof(int64_t) * k, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (k > 0 && trace->topology && trace->wl_size)
+        for (int64_t i = 0; i < k; ++i) trace->topology[i] = (int8_t)((int64_t)trace->wl_size[i] > H);
+    trace->recorded = k;
+    return IPGC_OK;
+}
+
+// Threshold of the schedule: a round is topology-driven iff its worklist holds more nodes.
+int64_t schedule_threshold(const Params &P, int64_t n) {
+    if (P.mode == IPGC_MODE_TOPOLOGY) return -1;      // |WL| > -1 always holds
+    if (P.mode == IPGC_MODE_DATA) return INT64_MAX;   // never
+    return P.threshold > 0 ? P.threshold : (6 * n) / 10;  // HYBRID and REBUILD
+}
+
+// One small graph, in one launch.  The verdict goes straight to pinned host memory (to scratch and from there
+// when the workspace is carved: such a call allocates nothing pinned).
+int color_small(Workspace &ws, hipStream_t s, const Params &P, const int32_t *rowptr, const int32_t *colidx, int64_t n,
+                int64_t m, int32_t *out_colors, int32_t *out_rounds, ipgc_trace *trace) {
+    SmallArgs a{};
+    a.rowptr = rowptr;
+    a.colidx = colidx;
+    a.out = out_colors;
+    a.n = n;
+    a.m = m;
+    a.check = P.check_ids ? 1 : 0;
+    if (trace) {
+        TRY(ws.trace.reserve(n));
+        TRY(ws.trace_deg.reserve(n));
+        a.trace = ws.trace.p;
+        a.trace_deg = ws.trace_deg.p;
+        a.trace_cap = n;
+    }
+    if (ws.borrowed) {
+        TRY(clear(ws.ct, sizeof(Counters), s));
+        a.ct = ws.ct;
+    } else {
+        *ws.host_ct = Counters{};
+        a.ct = ws.host_ct;
+    }
+    k_small<<<1, kCore, 0, s>>>(a);
+    HIP_TRY(hipGetLastError());
+    if (ws.borrowed) TRY(read_counters(ws, s));
+    else HIP_TRY(hipStreamSynchronize(s));
+    TRY(row_verdict(*ws.host_ct, m));
+    if (ws.host_ct->bad_ids) return fail(IPGC_EBADCSR, "a column id is outside [0, n)");
+    if (!ws.host_ct->finished) return fail(IPGC_ELIMIT, "rounds did not finish");
+    if (trace) TRY(read_trace(ws, s, trace, ws.host_ct->rounds, schedule_threshold(P, n)));
+    *out_rounds = ws.host_ct->rounds;
+    return IPGC_OK;
+}
+
 // Everything after the input is in place: d.rowptr, d.colidx, d.c and (for a
-// batch) d.gbase / d.gidx / d.node_off / d.grounds are set by the caller.
+// batch) d.gbase / d.gidx / d.node_off / d.grounds are set by the caller.  n_here: n, less a batch's nodes that
+// are colored elsewhere.
 template <class D>
-int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, int64_t m, int grid,
+int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, int64_t m, int64_t n_here, int grid,
         int coop, int32_t *out_rounds, ipgc_trace *trace) {
     using Off = typename D::OffT;
     int64_t span = 0;
@@ -423,10 +497,7 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
     ipgc_profile *prof = P.prof;
     Profiler pf{ws, s, prof ? prof->mask : 0u, {}, 0};
 
-    int64_t H;
-    if (P.mode == IPGC_MODE_TOPOLOGY) H = -1;          // |WL| > -1 always holds
-    else if (P.mode == IPGC_MODE_DATA) H = INT64_MAX;  // never
-    else H = P.threshold > 0 ? P.threshold : (6 * n) / 10;  // HYBRID and REBUILD
+    const int64_t H = schedule_threshold(P, n_here);
 
     d.cls = ws.cls.p;
     d.F = ws.F.p;
@@ -600,12 +671,8 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
     if (ws.host_ct->seg_overflow) return fail(IPGC_EHIP, "internal error: a worklist segment overflowed");
     const int32_t rounds = ws.host_ct->rounds;
     if (trace) {
-        const int64_t k = std::min<int64_t>(trace->capacity, rounds);
-        if (k > 0 && trace->wl_size)
-            HIP_TRY(hipMemcpyAsync(trace->wl_size, ws.trace.p, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
-        if (k > 0 && trace->wl_degree)
-            HIP_TRY(hipMemcpyAsync(trace->wl_degree, ws.trace_deg.p, sizeof(int64_t) * k, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        TRY(read_trace(ws, s, trace, rounds, H));
+        const int64_t k = trace->recorded;
         if (d.trace_topo) {  // per-graph schedules: the device counted the graphs of each kind
             const int64_t kt = std::min<int64_t>(k, d.topo_cap);
             std::vector<int32_t> tg((size_t)std::max<int64_t>(kt, 1));
@@ -614,10 +681,7 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
                 if (trace->topo_graphs) trace->topo_graphs[i] = tg[i];
                 if (trace->topology) trace->topology[i] = (int8_t)(tg[i] > 0);
             }
-        } else if (k > 0 && trace->topology && trace->wl_size) {
-            for (int64_t i = 0; i < k; ++i) trace->topology[i] = (int8_t)((int64_t)trace->wl_size[i] > H);
         }
-        trace->recorded = k;
     }
     if (prof) {
         HIP_TRY(hipStreamSynchronize(s));
@@ -662,6 +726,12 @@ int color_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t 
     Workspace &ws = workspace(dev);
     if (!ws.ct) TRY(ws.reserve(0, 0, 1, 1, kDefaultHubMin, false));
 
+    if (small_call(P) && small_graph(n, m)) {
+        TRY(color_small(ws, s, P, rowptr, colidx, n, m, out_colors, out_rounds, trace));
+        g_err[0] = 0;
+        return IPGC_OK;
+    }
+
     // rowptr[0] == 0 and rowptr[n] == m are checked by k_init, before any row is read
     int grid = 1, coop = 0;
     TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
@@ -670,7 +740,7 @@ int color_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t 
     d.colidx = colidx;
     d.c = out_colors;
     TRY(clear(ws.ct, sizeof(Counters), s));
-    TRY(run(ws, dev, s, P, d, n, m, grid, coop, out_rounds, trace));
+    TRY(run(ws, dev, s, P, d, n, m, n, grid, coop, out_rounds, trace));
     g_err[0] = 0;
     return IPGC_OK;
 }
@@ -709,9 +779,22 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
     std::lock_guard<std::mutex> lock(g_mutex);
     Workspace &ws = workspace(dev);
     if (!ws.ct) TRY(ws.reserve(0, 0, 1, 1, kDefaultHubMin, false));
-    TRY(ws.growptr.reserve(n + 1));
-    TRY(ws.gbase.reserve(n));
-    TRY(ws.gidx.reserve(n));
+    // Small graphs are colored by a workgroup each, largest first; the others as one union.  Per-round records
+    // are those of the whole batch's union, so calls that ask for them keep every graph in it.
+    std::vector<int32_t> small;  // alive until the call has synchronized
+    int64_t n_union = n, m_union = m;
+    if (small_call(P) && !P.per_graph && !trace) {
+        for (int64_t g = 0; g < graphs; ++g) {
+            const int64_t ng = node_off[g + 1] - node_off[g], mg = edge_off[g + 1] - edge_off[g];
+            if (!small_graph(ng, mg)) continue;
+            small.push_back((int32_t)g);
+            n_union -= ng;
+            m_union -= mg;
+        }
+        std::sort(small.begin(), small.end(), [&](int32_t x, int32_t y) {
+            return edge_off[x + 1] - edge_off[x] > edge_off[y + 1] - edge_off[y];
+        });
+    }
     TRY(ws.grounds.reserve(graphs));
     TRY(ws.node_off.reserve(graphs + 1));
     TRY(ws.edge_off.reserve(graphs + 1));
@@ -719,12 +802,42 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
     HIP_TRY(hipMemcpyAsync(ws.edge_off.p, edge_off, sizeof(int64_t) * (graphs + 1), hipMemcpyHostToDevice, s));
     TRY(clear(ws.grounds.p, sizeof(int32_t) * graphs, s));
     TRY(clear(ws.ct, sizeof(Counters), s));
+    if (!small.empty()) {
+        TRY(ws.small.reserve((int64_t)small.size()));
+        HIP_TRY(hipMemcpyAsync(ws.small.p, small.data(), sizeof(int32_t) * small.size(), hipMemcpyHostToDevice, s));
+        SmallArgs a{};
+        a.rowptr = rowptr_packed;
+        a.colidx = colidx_packed;
+        a.out = out_colors_packed;
+        a.node_off = ws.node_off.p;
+        a.edge_off = ws.edge_off.p;
+        a.order = ws.small.p;
+        a.grounds = ws.grounds.p;
+        a.ct = ws.ct;
+        a.check = P.check_ids ? 1 : 0;
+        k_small<<<(int)small.size(), kCore, 0, s>>>(a);
+        HIP_TRY(hipGetLastError());
+    }
+    if (n_union == 0) {  // every graph was small
+        HIP_TRY(hipMemcpyAsync(out_rounds, ws.grounds.p, sizeof(int32_t) * graphs, hipMemcpyDeviceToHost, s));
+        TRY(read_counters(ws, s));
+        int rc = row_verdict(*ws.host_ct, m);
+        if (rc == IPGC_OK && ws.host_ct->bad_ids) rc = fail(IPGC_EBADCSR, "a column id is outside [0, n)");
+        if (rc != IPGC_OK)
+            for (int64_t g = 0; g < graphs; ++g) out_rounds[g] = -1;
+        else
+            g_err[0] = 0;
+        return rc;
+    }
+    TRY(ws.growptr.reserve(n + 1));
+    TRY(ws.gbase.reserve(n));
+    TRY(ws.gidx.reserve(n));
     k_batch_union<<<(int)std::min<int64_t>(graphs, 16384), kPrepBlock, 0, s>>>(
-        ws.node_off.p, ws.edge_off.p, rowptr_packed, graphs, ws.growptr.p, ws.gbase.p, ws.gidx.p, ws.ct);
+        ws.node_off.p, ws.edge_off.p, rowptr_packed, graphs, small.empty() ? -1 : kSmallNodes, kSmallEntries, ws.growptr.p, ws.gbase.p, ws.gidx.p, ws.ct);
     HIP_TRY(hipGetLastError());
 
     int grid = 1, coop = 0;
-    TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
+    TRY(round_grid(ws, dev, P, n_union, m_union, false, &grid, &coop));
     auto setup = [&](auto &d) {
         d.rowptr = ws.growptr.p;
         d.colidx = colidx_packed;
@@ -771,11 +884,11 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
             d.trace_topo = ws.trace_topo.p;
             d.topo_cap = tcap;
         }
-        TRY(run(ws, dev, s, P, d, n, m, grid, coop, &rounds, trace));
+        TRY(run(ws, dev, s, P, d, n, m, n, grid, coop, &rounds, trace));
     } else {
         DevT<int64_t> d{};
         setup(d);
-        TRY(run(ws, dev, s, P, d, n, m, grid, coop, &rounds, trace));
+        TRY(run(ws, dev, s, P, d, n, m, n_union, grid, coop, &rounds, trace));
     }
     HIP_TRY(hipMemcpyAsync(out_rounds, ws.grounds.p, sizeof(int32_t) * graphs, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -850,13 +963,18 @@ int color_noalloc_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, 
         rc = ws.carve(base, kStaticScratchBytes, n, m, grid, prep_grid, P.hub_min, P.full, &used);
     }
     TRY(rc);
+    if (small_call(P) && small_graph(n, m)) {
+        TRY(color_small(ws, s, P, rowptr, colidx, n, m, out_colors, out_rounds, trace));
+        g_err[0] = 0;
+        return IPGC_OK;
+    }
 
     DevT<int32_t> d{};
     d.rowptr = rowptr;
     d.colidx = colidx;
     d.c = out_colors;
     TRY(clear(ws.ct, sizeof(Counters), s));  // the array keeps the previous call's contents
-    TRY(run(ws, dev, s, P, d, n, m, grid, coop, out_rounds, trace));
+    TRY(run(ws, dev, s, P, d, n, m, n, grid, coop, out_rounds, trace));
     g_err[0] = 0;
     return IPGC_OK;
 }

@@ -177,7 +177,8 @@ struct DevT {
     const Off *rowptr;       // row starts, n + 1 entries (a batch: union row starts)
     const int32_t *colidx;   // column indices (a batch: ids local to each graph)
     const int32_t *gbase;    // a batch: first global id of each node's graph (null for one graph)
-    const int32_t *gidx;     // a batch: graph index of each node (null for one graph)
+    const int32_t *gidx;     // a batch: graph index of each node (null for one graph; negative: the node's
+                             // graph is colored elsewhere, by k_small)
     const int64_t *gend;     // a batch: one past the last global id of each graph
     int32_t *grounds;        // a batch: rounds per graph (the last round one of its nodes committed)
     int32_t *gleft;          // a server: uncommitted nodes per graph (null otherwise)
@@ -504,6 +505,10 @@ __global__ __launch_bounds__(kPrepBlock) void k_init(D d, int8_t *cls, int32_t s
     int chunks = 0;  // row chunks of class-M nodes (their rings are built a chunk per wavefront)
     int bad = 0, bad_id = 0, unsorted = 0;
     for (int64_t v = lo + threadIdx.x; v < hi; v += blockDim.x) {
+        if (d.gidx && d.gidx[v] < 0) {
+            cls[v] = -1;
+            continue;
+        }
         // Round 1 assigns color 1 to every node (no neighbour is committed yet), so the state
         // starts there: tentative color 1, and round 1 skips its assign step.
         d.c[v] = -1;
@@ -610,7 +615,7 @@ __global__ __launch_bounds__(1024) void k_offsets(D d, int32_t prep_grid) {
         int32_t off[kNumClasses + 1];
         off[0] = 0;
         for (int k = 1; k < kNumClasses; ++k) off[k] = d.block_cnt[k * prep_grid];
-        off[kNumClasses] = d.n;
+        off[kNumClasses] = base;  // n, less the nodes colored elsewhere
         int64_t so = 0;
         for (int k = 0; k < kNumClasses; ++k) {
             d.ct->static_off[k] = off[k];
@@ -621,7 +626,7 @@ __global__ __launch_bounds__(1024) void k_offsets(D d, int32_t prep_grid) {
             d.ct->seg_off[k] = so;
             so += (int64_t)cap * d.grid;
         }
-        d.ct->static_off[kNumClasses] = d.n;
+        d.ct->static_off[kNumClasses] = base;
         d.ct->seg_off[kNumClasses] = so;
         d.ct->static_ident = d.n > 0 && (d.ct->class_n[kL] == d.n || d.ct->class_n[kW] == d.n);
         if (d.hub_pre) d.hub_pre[d.ct->class_n[kM]] = d.ct->hub_chunks;
@@ -997,9 +1002,11 @@ __global__ __launch_bounds__(kPrepBlock) void k_full_check(D d, int64_t v_lo, in
 // g shifted by its first entry), the first global id of each node's graph,
 // and each node's graph index.  A workgroup per graph at a time; also checks
 // each graph's row pointers (local rowptr[0] == 0, rowptr[n_g] == m_g,
-// non-decreasing) and flags bad_rows.
+// non-decreasing) and flags bad_rows.  Graphs of at most small_n nodes and small_m entries (small_n < 0:
+// none) are colored elsewhere: their nodes get a negative graph index.
 static __global__ __launch_bounds__(kPrepBlock) void k_batch_union(const int64_t *node_off, const int64_t *edge_off,
                                                             const int32_t *rowptr_packed, int64_t graphs,
+                                                            int64_t small_n, int64_t small_m,
                                                             int64_t *growptr, int32_t *gbase, int32_t *gidx,
                                                             Counters *ct) {
     int bad = 0;
@@ -1016,7 +1023,7 @@ static __global__ __launch_bounds__(kPrepBlock) void k_batch_union(const int64_t
                 bad |= e < a || a < 0 || e > mg;
                 growptr[n0 + lv] = e0 + a;
                 gbase[n0 + lv] = (int32_t)n0;
-                gidx[n0 + lv] = (int32_t)g;
+                gidx[n0 + lv] = ng <= small_n && mg <= small_m ? -1 : (int32_t)g;
             }
         }
     }

@@ -1,0 +1,430 @@
+// Small graphs: one workgroup colors a whole graph, its state in shared memory.
+//
+// The cooperative kernel spends 20 to 40 us on a round however small the graph is (grid barriers, chains of
+// dependent loads from memory), and a call adds six launches and two host waits.  Here a graph of at most
+// kSmallNodes nodes is checked and colored in one launch: while more than kCore nodes are uncolored, rounds
+// walk a worklist with the colors, the forbidden-color masks and both lists in shared memory (only the
+// rows come from memory, mostly the L2); then the uncolored nodes go on in the core (ipgc_core.hpp).
+// Graphs of up to kCore nodes start there.  A batch runs a workgroup per graph, largest first.
+#pragma once
+
+#include "ipgc_core.hpp"
+
+namespace ipgc {
+
+// 14 bytes of shared memory a node: mask 8, color 2, two list entries 4.
+constexpr int kSmallNodes = 10240;
+constexpr int kSmallLight = 32;  // rows up to this length: a thread each; longer ones: 16 lanes or a wavefront
+
+struct SmallLists {
+    uint64_t mask[kSmallNodes];     // bit t - 1: a committed neighbour has color t (t <= 64)
+    int16_t c[kSmallNodes];         // > 0 committed, -t tentative
+    uint16_t wl[2][kSmallNodes];    // worklists: short rows from the front, long rows from the back
+};
+
+struct SmallShared {
+    union {
+        SmallLists a;
+        CoreShared core;
+    };
+    uint64_t bits[kSmallNodes / 64];  // uncolored nodes, when the core starts
+    int32_t pre[kSmallNodes / 64];    // and the number of them before each word
+    int nl[2], nw[2];                 // entries of each worklist, short and long rows
+    int bad, descents, starts;
+    unsigned long long deg;
+};
+static_assert(sizeof(SmallShared) <= 160 * 1024 - 1024, "one workgroup's shared memory");
+
+struct SmallArgs {
+    const int32_t *rowptr;     // one graph's CSR, or a packed batch's
+    const int32_t *colidx;
+    int32_t *out;
+    int64_t n, m;              // one graph
+    const int64_t *node_off;   // a batch: offsets of its graphs (null for one graph)
+    const int64_t *edge_off;
+    const int32_t *order;      // a batch: the graph of each workgroup
+    int32_t *grounds;          // a batch: rounds per graph
+    Counters *ct;              // verdicts; one graph: also finished, rounds and the CSR's ends
+    int32_t *trace;            // one graph: per-round sizes and degree sums (null: not kept)
+    int64_t *trace_deg;
+    int64_t trace_cap;
+    int32_t check;             // check the column ids
+};
+
+// The colors that the committed neighbours of a node hold among the 64 from x on (bit k: color x + k), from
+// its row: for nodes whose mask says no more.
+struct SmallRow {
+    const int32_t *rp, *ci, *out;  // out: colors, 0 for nodes the core has not committed yet
+    __device__ __forceinline__ uint64_t taken(const CoreState &s, int32_t x) const {
+        uint64_t m = 0;
+        for (int32_t k = rp[s.v]; k < rp[s.v + 1]; ++k) {
+            const uint32_t q = (uint32_t)(out[ci[k]] - x);
+            if (q < 64) m |= 1ull << q;
+        }
+        return m;
+    }
+};
+
+// First free color above 64 of node v, whose mask is full.
+__device__ __forceinline__ int32_t small_pull(const SmallShared &sh, const SmallArgs &, const int32_t *rp, const int32_t *ci, int v) {
+    for (int32_t x = max(kMaskColors + 1, -(int32_t)sh.a.c[v]);; x += 64) {
+        uint64_t m = 0;
+        for (int32_t k = rp[v]; k < rp[v + 1]; ++k) {
+            const uint32_t q = (uint32_t)((int32_t)sh.a.c[ci[k]] - x);
+            if (q < 64) m |= 1ull << q;
+        }
+        if (m != ~0ull) return x + __ffsll((unsigned long long)~m) - 1;
+    }
+}
+
+// Places for the flagged lanes of a wavefront after *count (shared): one atomic per wavefront.
+__device__ __forceinline__ int wave_append(bool flag, int *count) {
+    const uint64_t m = __ballot(flag);
+    int at = 0;
+    if (m) {
+        if (lane_id() == 0) at = atomicAdd(count, (int)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+    }
+    return at + __popcll(m & lanes_below());
+}
+
+// One round's conflict tests, commits and pushes of the short rows, a lane each, two in flight per lane.
+__device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, const int32_t *ci, int32_t *out, int p,
+                                            bool sorted, bool deg) {
+    constexpr int K = 2, C = 4;
+    const int nl = sh.nl[p];
+    const uint16_t *cur = sh.a.wl[p];
+    uint16_t *nxt = sh.a.wl[p ^ 1];
+    for (int i0 = 0; i0 < nl; i0 += K * kCore) {
+        int v[K], t[K], b[K], e[K];
+        uint32_t lose = 0, done = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = i0 + j * kCore + (int)threadIdx.x;
+            v[j] = i < nl ? (int)cur[i] : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            t[j] = v[j] >= 0 ? -(int)sh.a.c[v[j]] : 0;
+            b[j] = v[j] >= 0 ? rp[v[j]] : 0;
+            e[j] = v[j] >= 0 ? rp[v[j] + 1] : 0;
+            done |= (b[j] >= e[j] ? 1u : 0u) << j;
+        }
+        for (int q0 = 0; done != (1u << K) - 1; q0 += C) {
+            int u[K][C];
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+#pragma unroll
+                for (int q = 0; q < C; ++q)
+                    u[j][q] = !(done >> j & 1u) && b[j] + q0 + q < e[j] ? ci[b[j] + q0 + q] : INT32_MAX;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                bool past = false;
+#pragma unroll
+                for (int q = 0; q < C; ++q) {
+                    if (u[j][q] >= v[j]) past |= sorted;
+                    else if (abs((int)sh.a.c[u[j][q]]) == t[j]) lose |= 1u << j;
+                }
+                if (past || (lose >> j & 1u) || b[j] + q0 + C >= e[j]) done |= 1u << j;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const bool l = v[j] >= 0 && (lose >> j & 1u);
+            const int at = wave_append(l, &sh.nl[p ^ 1]);
+            if (l) nxt[at] = (uint16_t)v[j];
+            if (v[j] < 0 || l) continue;
+            sh.a.c[v[j]] = (int16_t)t[j];
+            out[v[j]] = t[j];
+            if (deg) atomicAdd(&sh.deg, 0ull - (unsigned long long)(e[j] - b[j]));
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (v[j] < 0 || (lose >> j & 1u) || t[j] > kMaskColors) continue;
+            const unsigned long long bit = 1ull << (t[j] - 1);
+            for (int k = b[j]; k < e[j]; k += C) {
+                int u[C];
+#pragma unroll
+                for (int q = 0; q < C; ++q) u[q] = k + q < e[j] ? ci[k + q] : -1;
+#pragma unroll
+                for (int q = 0; q < C; ++q)
+                    if (u[q] >= 0) atomicOr((unsigned long long *)&sh.a.mask[u[q]], bit);
+            }
+        }
+    }
+}
+
+// The same for the long rows, by groups of S lanes (16, so that four rows overlap in a wavefront, or a
+// wavefront when there are few of them).
+__device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, const int32_t *ci, int32_t *out, int p,
+                                           bool sorted, bool deg) {
+    constexpr int C = 4;
+    const int nw = sh.nw[p], S = nw >= kCore / kWave * 4 ? 16 : kWave, per = kCore / S;
+    const int lane = lane_id(), gl = threadIdx.x % S;
+    const uint64_t gm = S == kWave ? ~0ull : 0xFFFFull << (lane - gl);
+    const uint16_t *cur = sh.a.wl[p];
+    uint16_t *nxt = sh.a.wl[p ^ 1];
+    for (int i0 = 0; i0 < nw; i0 += per) {  // the same for the whole workgroup
+        const int i = i0 + (int)threadIdx.x / S;
+        const int v = i < nw ? (int)cur[kSmallNodes - 1 - i] : -1;
+        const int t = v >= 0 ? -(int)sh.a.c[v] : 0, b = v >= 0 ? rp[v] : 0, e = v >= 0 ? rp[v + 1] : 0;
+        bool lose = false, more = b < e;
+        for (int k0 = b; __ballot(more); k0 += C * S) {  // the same for the whole wavefront
+            int u[C];
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const int k = k0 + q * S + gl;
+                u[q] = more && k < e ? ci[k] : INT32_MAX;
+            }
+            bool hit = false, past = false;
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                if (u[q] >= v) past |= sorted;
+                else hit |= abs((int)sh.a.c[u[q]]) == t;
+            }
+            lose = lose || (__ballot(hit) & gm) != 0;
+            more = more && !lose && !(__ballot(past) & gm) && k0 + C * S < e;
+        }
+        const bool l = v >= 0 && lose && gl == 0;
+        const int at = wave_append(l, &sh.nw[p ^ 1]);
+        if (l) nxt[kSmallNodes - 1 - at] = (uint16_t)v;
+        if (v < 0 || lose) continue;
+        if (gl == 0) {
+            sh.a.c[v] = (int16_t)t;
+            out[v] = t;
+            if (deg) atomicAdd(&sh.deg, 0ull - (unsigned long long)(e - b));
+        }
+        if (t > kMaskColors) continue;
+        const unsigned long long bit = 1ull << (t - 1);
+        for (int k0 = b + gl; k0 < e; k0 += C * S) {
+            int u[C];
+#pragma unroll
+            for (int q = 0; q < C; ++q) u[q] = k0 + q * S < e ? ci[k0 + q * S] : -1;
+#pragma unroll
+            for (int q = 0; q < C; ++q)
+                if (u[q] >= 0) atomicOr((unsigned long long *)&sh.a.mask[u[q]], bit);
+        }
+    }
+}
+
+static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
+    __shared__ SmallShared sh;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int32_t g = a.order ? a.order[blockIdx.x] : 0;
+    const int64_t n0 = a.node_off ? a.node_off[g] : 0, e0 = a.node_off ? a.edge_off[g] : 0;
+    const int32_t n = (int32_t)(a.node_off ? a.node_off[g + 1] - n0 : a.n);
+    const int64_t m = a.node_off ? a.edge_off[g + 1] - e0 : a.m;
+    const int32_t *rp = a.rowptr + n0 + g, *ci = a.colidx + e0;
+    int32_t *out = a.out + n0;
+
+    // Checks: the CSR's ends, row pointers non-decreasing inside [0, m], ids inside [0, n); and whether every
+    // row is sorted: the entries not above their predecessor are then all first entries of rows.
+    if (tid == 0) {
+        sh.bad = sh.descents = sh.starts = 0;
+        sh.nl[0] = sh.nw[0] = 0;
+    }
+    __syncthreads();
+    int bad = 0, starts = 0, descents = 0;
+    for (int v = tid; v < n; v += kCore) {
+        const int64_t b = rp[v], e = rp[v + 1];
+        if (b < 0 || e < b || e > m) bad |= 1;
+        else if (b > 0 && b < e) starts += ci[b] <= ci[b - 1];
+    }
+    if (tid == 0) {
+        if (rp[0] != 0 || rp[n] != m) bad |= 4;
+        if (!a.node_off) {
+            a.ct->ends[0] = rp[0];
+            a.ct->ends[1] = rp[n];
+        }
+    }
+    constexpr int P = 8;
+    for (int64_t k0 = tid; k0 < m; k0 += P * kCore) {
+        int32_t u[P], w[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int64_t k = k0 + q * kCore;
+            u[q] = k < m ? ci[k] : 0;
+            w[q] = k > 0 && k < m ? ci[k - 1] : INT32_MIN;
+        }
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int64_t k = k0 + q * kCore;
+            if (k >= m) continue;
+            if (a.check && (uint32_t)u[q] >= (uint32_t)n) bad |= 2;
+            descents += k > 0 && u[q] <= w[q];
+        }
+    }
+    if (bad) atomicOr(&sh.bad, bad);
+    starts = (int)wave_sum(starts);
+    descents = (int)wave_sum(descents);
+    if (lane == 0 && starts) atomicAdd(&sh.starts, starts);
+    if (lane == 0 && descents) atomicAdd(&sh.descents, descents);
+    __syncthreads();
+    bad = sh.bad;
+    const bool sorted = sh.starts == sh.descents;
+    if (bad) {
+        if (tid == 0) {
+            if (bad & 4) {
+                if (a.node_off) a.ct->bad_rows = 1;
+                else a.ct->bad_ends = 1;
+            }
+            if (bad & 1) a.ct->bad_rows = 1;
+            if (bad & 2) a.ct->bad_ids = 1;
+        }
+        return;
+    }
+
+    // Rounds over the worklist while more than kCore nodes are uncolored.
+    int32_t r = 1;
+    int nact = n, p = 0;
+    int64_t deg = m;
+    const bool keep = a.trace != nullptr;
+    CoreState s;
+    if (n > kCore) {
+        for (int v0 = 0; v0 < n; v0 += kCore) {
+            const int v = v0 + tid;
+            const bool has = v < n, wide = has && rp[v + 1] - rp[v] > kSmallLight;
+            if (has) {
+                sh.a.mask[v] = 0;
+                sh.a.c[v] = -1;
+            }
+            const int at = wave_append(has && !wide, &sh.nl[0]), aw = wave_append(wide, &sh.nw[0]);
+            if (wide) sh.a.wl[0][kSmallNodes - 1 - aw] = (uint16_t)v;
+            else if (has) sh.a.wl[0][at] = (uint16_t)v;
+        }
+        if (tid == 0) sh.deg = (unsigned long long)m;
+        __syncthreads();
+        while (nact > kCore) {
+            if (keep && tid == 0 && r - 1 < a.trace_cap) {
+                a.trace[r - 1] = nact;
+                a.trace_deg[r - 1] = (int64_t)sh.deg;
+            }
+            const int nl = sh.nl[p], nw = sh.nw[p];
+            if (r > 1) {  // round 1's tentative colors are all 1
+                for (int i = tid; i < nl + nw; i += kCore) {
+                    const int v = i < nl ? sh.a.wl[p][i] : sh.a.wl[p][kSmallNodes - 1 - (i - nl)];
+                    const uint64_t free = ~sh.a.mask[v];
+                    sh.a.c[v] = (int16_t)-(free ? __ffsll((unsigned long long)free) : small_pull(sh, a, rp, ci, v));
+                }
+            }
+            if (tid == 0) sh.nl[p ^ 1] = sh.nw[p ^ 1] = 0;
+            core_sync();
+            small_wide(sh, rp, ci, out, p, sorted, keep);
+            small_light(sh, rp, ci, out, p, sorted, keep);
+            core_sync();
+            p ^= 1;
+            ++r;
+            nact = sh.nl[p] + sh.nw[p];
+            core_sync();  // the counts are cleared in the next round, the degree sum read
+        }
+        deg = (int64_t)sh.deg;
+        // hand over to the core: ranks from a bit per uncolored node, the nodes' state through shared memory
+        for (int k = tid; k < kSmallNodes / 64; k += kCore) sh.bits[k] = 0;
+        __syncthreads();
+        const int nl = sh.nl[p];
+        int v = -1;
+        if (tid < nact) v = tid < nl ? sh.a.wl[p][tid] : sh.a.wl[p][kSmallNodes - 1 - (tid - nl)];
+        const int32_t t = v >= 0 ? -(int32_t)sh.a.c[v] : 0;
+        const uint64_t mask = v >= 0 ? sh.a.mask[v] : 0;
+        if (v >= 0) {
+            atomicOr((unsigned long long *)&sh.bits[v >> 6], 1ull << (v & 63));
+            out[v] = 0;  // not committed (read when a color window has to be filled from the row)
+        }
+        __syncthreads();
+        int total;
+        const int pc = tid < kSmallNodes / 64 ? __popcll(sh.bits[tid]) : 0;
+        const int ex = block_scan(pc, &total);
+        if (tid < kSmallNodes / 64) sh.pre[tid] = ex;
+        __syncthreads();
+        uint64_t *stage = sh.core.adj;  // 3 words a node
+        if (v >= 0) {
+            const int rank = sh.pre[v >> 6] + __popcll(sh.bits[v >> 6] & ((1ull << (v & 63)) - 1));
+            stage[rank] = (uint64_t)(uint32_t)v;
+            stage[kCore + rank] = (uint64_t)(uint32_t)t;
+            stage[2 * kCore + rank] = mask;
+        }
+        __syncthreads();
+        if (tid < nact) {
+            s.v = (int32_t)stage[tid];
+            s.base = (int32_t)stage[kCore + tid] - 1;
+            const uint64_t mk = stage[2 * kCore + tid];
+            s.lo = s.base < 64 ? mk >> s.base : 0;
+            if (r > kMaskColors + 1) {  // colors above 64 may be committed: the row says which
+                const SmallRow row{rp, ci, out};
+                s.lo = row.taken(s, s.base + 1);
+                s.hi = row.taken(s, s.base + 65);
+            }
+        }
+    } else if (tid < n) {
+        s.v = tid;
+        out[tid] = 0;
+    }
+    __syncthreads();
+    if (nact > 0) {  // false for a graph without nodes alone
+        // The matrix: short rows by their thread, long ones by 16 lanes or a wavefront.
+        for (int k = tid; k < kCoreWords * kCoreStride; k += kCore) sh.core.adj[k] = 0;
+        if (tid == 0) sh.core.nwin = 0;
+        __syncthreads();
+        const bool direct = n <= kCore;
+        const auto put = [&](int rank, int32_t u) {
+            int q = u;
+            if (!direct) {
+                const uint64_t word = sh.bits[u >> 6], bit = 1ull << (u & 63);
+                if (!(word & bit)) return;
+                q = sh.pre[u >> 6] + __popcll(word & (bit - 1));
+            }
+            atomicOr((unsigned long long *)&sh.core.adj[(q >> 6) * kCoreStride + rank], 1ull << (q & 63));
+        };
+        const int b = s.v >= 0 ? rp[s.v] : 0, e = s.v >= 0 ? rp[s.v + 1] : 0;
+        s.deg = e - b;
+        const bool wide = s.deg > kSmallLight;
+        const int at = wave_append(wide, &sh.core.nwin);
+        if (wide) sh.core.t[at] = tid;
+        else {
+            for (int k = b; k < e; k += 4) {
+                int32_t u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) u[q] = k + q < e ? ci[k + q] : -1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (u[q] >= 0) put(tid, u[q]);
+            }
+        }
+        int32_t *node = reinterpret_cast<int32_t *>(sh.core.bucket);  // node of each rank, until the rounds start
+        if (tid < nact) node[tid] = s.v;
+        __syncthreads();
+        const int nw = sh.core.nwin, S = nw >= kCore / kWave * 4 ? 16 : kWave, gl = tid % S;
+        for (int i = tid / S; i < nw; i += kCore / S) {
+            const int rank = sh.core.t[i], v = node[rank];
+            const int e2 = rp[v + 1];
+            for (int k = rp[v] + gl; k < e2; k += 4 * S) {
+                int32_t u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) u[q] = k + q * S < e2 ? ci[k + q * S] : -1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (u[q] >= 0) put(rank, u[q]);
+            }
+        }
+        __syncthreads();
+    }
+    int64_t nodes = 0;
+    const int32_t last = core_rounds(
+        SmallRow{rp, ci, out}, sh.core, s, r, nact, deg, &nodes,
+        [&](const CoreState &x, int32_t) { out[x.v] = x.t; },
+        [&](int32_t q, int32_t active, int64_t dsum) {
+            if (keep && q - 1 < a.trace_cap) {
+                a.trace[q - 1] = active;
+                a.trace_deg[q - 1] = dsum;
+            }
+        });
+    if (tid == 0) {
+        if (a.grounds) a.grounds[g] = last;
+        if (!a.node_off) {
+            a.ct->rounds = last;
+            a.ct->finished = 1;
+        }
+    }
+}
+
+}  // namespace ipgc

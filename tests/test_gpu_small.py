@@ -1,0 +1,118 @@
+"""Graphs that one workgroup colors (at most 10 240 nodes, default kernel options): against the oracle at the
+edges of its lists, matrix and masks, with unsorted rows, in batches with larger graphs, and its verdicts."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+from tests.test_gpu_core import cliques
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+
+
+def dev(*arrays):
+    return [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in arrays]
+
+
+def check(g, rowptr=None, colidx=None, noalloc=False, **kw):
+    import paper_1912_01478_amd as ip
+    ref = oracle.color_graph(g.rowptr, g.colidx)
+    rp, ci = dev(g.rowptr if rowptr is None else rowptr, g.colidx if colidx is None else colidx)
+    print("[gpu] small %s n=%d m=%d %s" % (g.name, g.n, g.m, kw), flush=True)
+    for trace in (False, True):
+        if noalloc:
+            out = torch.empty(g.n, dtype=torch.int32, device="cuda")
+            res = ip.color_graph_noalloc(rp, ci, out=out, trace=trace, **kw)
+        else:
+            res = ip.color_graph(rp, ci, trace=trace, **kw)
+        assert res.rounds == ref.rounds
+        bad = np.nonzero(res.colors.cpu().numpy() != ref.colors)[0]
+        assert bad.size == 0, "node %d" % bad[0]
+        if trace:
+            assert list(res.wl_sizes) == list(ref.wl_sizes)
+            assert list(res.wl_degrees) == list(ref.wl_degree_sums)
+
+
+# Node counts at the edges of a wavefront, the core and the lists; row lengths at 32 and 33; more than 64 colors
+# while the worklist is still in the lists (14 cliques of 150: 77 rounds before the core takes over).
+SIZES = [gg.erdos_renyi(n, d, gg.key(80, n + int(d)), name="er%d_%d" % (n, d))
+         for n, d in ((1, 0), (2, 1), (63, 5), (64, 5), (65, 60), (1023, 9), (1024, 30), (1025, 32), (2048, 33), (5003, 20),
+                      (10239, 7), (10240, 40), (10241, 7))]
+SHAPES = [gg.rmat(10, 16, gg.key(81, 0)), gg.rmat(13, 16, gg.key(81, 1)), gg.rmat(14, 12, gg.key(81, 2), n=10007), cliques(14, 150),
+          cliques(3, 341), cliques(60, 33, 100), cliques(60, 34, 100), gg.complete(1024), gg.complete(1025), gg.star(10239, 0),
+          gg.star(10239, 10239), gg.star(5000, 2500), gg.path(10240), gg.crown(700), gg.empty(1), gg.empty(10240),
+          gg.complete_bipartite(3, 9000), gg.road_knn(9001, gg.key(81, 3))]
+
+
+@pytest.mark.parametrize("g", SIZES + SHAPES, ids=lambda g: g.name)
+def test_small_graphs(g):
+    check(g)
+    check(g, mode="data", noalloc=True)
+
+
+@pytest.mark.parametrize("g", SIZES[5:9] + SHAPES[:6], ids=lambda g: g.name)
+def test_small_graphs_with_unsorted_rows(g):
+    rp, ci = gg.shuffle_rows(g, 5)
+    check(g, rp, ci)
+    check(g, rp, ci, validate=1)
+
+
+def test_small_graphs_with_self_loops_and_repeated_entries():
+    g = gg.rmat(12, 8, gg.key(82, 0))
+    deg = g.degrees()
+    rp = np.zeros(g.n + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(2 * deg + 1)
+    ci = np.concatenate([np.concatenate([np.repeat(g.colidx[g.rowptr[v]:g.rowptr[v + 1]], 2), [v]]) for v in range(g.n)]).astype(np.int32)
+    ref = oracle.color_graph(g.rowptr, g.colidx)
+    import paper_1912_01478_amd as ip
+    res = ip.color_graph(*dev(rp, ci))
+    assert res.rounds == ref.rounds and np.array_equal(res.colors.cpu().numpy(), ref.colors)
+
+
+def test_batches_of_small_and_larger_graphs():
+    """Small graphs apart from the union, alone, and none of them; every graph's own colors and rounds."""
+    import paper_1912_01478_amd as ip
+    large = [gg.rmat(14, 8, gg.key(83, 0)), gg.erdos_renyi(30011, 6.0, gg.key(83, 1)), gg.erdos_renyi(10241, 40.0, gg.key(83, 2))]
+    small = SIZES[:9] + SHAPES[:3] + [gg.empty(0), gg.empty(7), cliques(14, 150), gg.complete(300)]
+    for graphs in (small, [small[3], large[0], small[9], gg.empty(0), large[1], large[2], small[11]], large, [gg.empty(0)] * 3 + [small[2]]):
+        refs = [oracle.color_graph(g.rowptr, g.colidx) for g in graphs]
+        node_off, edge_off, rp, ci = ip.pack_graphs([(g.rowptr, g.colidx) for g in graphs])
+        rp, ci = dev(rp, ci)
+        print("[gpu] small batch of %d graphs" % len(graphs), flush=True)
+        for kw in (dict(), dict(mode="data"), dict(mode="topology"), dict(mode="rebuild"), dict(trace=True), dict(workgroups=5)):
+            out = torch.full((int(node_off[-1]),), -7, dtype=torch.int32, device="cuda")
+            res = ip.color_graphs_batched(rp, ci, node_off, edge_off, out=out, **kw)
+            for k, (g, ref) in enumerate(zip(graphs, refs)):
+                assert np.array_equal(res.graph(k).cpu().numpy(), ref.colors), (g.name, kw)
+                assert res.rounds[k] == ref.rounds, (g.name, kw)
+
+
+def test_verdicts():
+    """The errors of the general path, alone and in a batch; the next call is right."""
+    import paper_1912_01478_amd as ip
+    g, h = gg.erdos_renyi(3000, 8.0, gg.key(84, 0)), gg.erdos_renyi(20000, 8.0, gg.key(84, 1))
+    rp, ci = dev(g.rowptr, g.colidx)
+    changes = [("ci", 0, -1), ("ci", g.m - 1, g.n), ("ci", g.m // 2, 2**31 - 1), ("rp", 0, 1), ("rp", g.n, g.m - 1),
+               ("rp", g.n // 2, -1), ("rp", g.n // 2, g.m + 5), ("rp", 7, int(g.rowptr[8]) + 1)]
+    for which, at, value in changes:
+        a, b = rp.clone(), ci.clone()
+        (a if which == "rp" else b)[at] = value
+        out = torch.empty(g.n, dtype=torch.int32, device="cuda")
+        for call in (lambda: ip.color_graph(a, b), lambda: ip.color_graph_noalloc(a, b, out=out)):
+            with pytest.raises(ip.IpgcError) as e:
+                call()
+            assert e.value.code == ip.EBADCSR, (which, at, value)
+        for other in ([], [(h.rowptr, h.colidx)]):
+            bad = [(a.cpu().numpy(), b.cpu().numpy())]
+            node_off, edge_off, prp, pci = ip.pack_graphs([(g.rowptr, g.colidx)] + bad + other)
+            with pytest.raises(ip.IpgcError) as e:
+                ip.color_graphs_batched(*dev(prp, pci), node_off, edge_off)
+            assert e.value.code == ip.EBADCSR, (which, at, value)
+    check(g)
