@@ -139,7 +139,7 @@ __device__ __forceinline__ void core_compact(CoreShared &sh, CoreState &s, bool 
 // Rounds r0, r0 + 1, ... until every node of the core is colored, by the whole workgroup (kCore threads;
 // thread i holds the node of rank i, s.v < 0 for none).  commit(s, round) stores a node's color;
 // record(round, nodes, degree sum) is called by thread 0 at the start of every round with the uncolored
-// nodes.  Returns the number of the last round; *sum_nodes: the uncolored nodes summed over the rounds.
+// nodes (their degrees are summed only if `degrees`).  Returns the number of the last round; *sum_nodes: the uncolored nodes summed over the rounds.
 //
 // A node loses iff a smaller uncolored neighbour has the same tentative color.  Candidates are the
 // neighbours whose color agrees modulo 128, found word by word from the bucket sets, and compared exactly.
@@ -147,7 +147,7 @@ __device__ __forceinline__ void core_compact(CoreShared &sh, CoreState &s, bool 
 // the winners and their colors are the same for the whole wavefront, so they come from scalar registers.
 template <class Far, class Commit, class Record>
 __device__ __forceinline__ int32_t core_rounds(const Far &far, CoreShared &sh, CoreState s, int32_t r0, int nact,
-                                               int64_t degsum, int64_t *sum_nodes, Commit &&commit, Record &&record) {
+                                               bool degrees, int64_t degsum, int64_t *sum_nodes, Commit &&commit, Record &&record) {
     const int i = threadIdx.x, w = i / kWave, lane = lane_id();
     bool act = s.v >= 0;
     int span = kCore;  // threads that may hold a node
@@ -192,22 +192,24 @@ __device__ __forceinline__ int32_t core_rounds(const Far &far, CoreShared &sh, C
             sh.wdeg = 0;
         }
         bool lose = false;
+        // all colors are at most r, so up to round 128 the buckets are exact
         if (act) {
             for (int w0 = 0; w0 <= rw && !lose; w0 += 4) {
                 uint64_t x[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {  // the four words' loads are in flight together
-                    const int ww = w0 + q;
-                    x[q] = ww <= rw ? sh.adj[ww * kCoreStride + s.rank] & sh.bucket[ww * kCoreBuckets + h] : 0;
+                    const int ww = w0 + q;  // past rw: smaller ranks only, so masked out below
+                    x[q] = sh.adj[ww * kCoreStride + s.rank] & sh.bucket[ww * kCoreBuckets + h];
                     if (ww == rw) x[q] &= rbit - 1;
+                    if (ww > rw) x[q] = 0;
                 }
-                while ((x[0] | x[1] | x[2] | x[3]) && !lose) {
-                    const int q = x[0] ? 0 : x[1] ? 1 : x[2] ? 2 : 3;
-                    const uint64_t y = x[0] ? x[0] : x[1] ? x[1] : x[2] ? x[2] : x[3];
-                    lose = sh.t[(w0 + q) * 64 + __ffsll((unsigned long long)y) - 1] == s.t;
+                if (r <= kCoreBuckets) {
+                    lose = (x[0] | x[1] | x[2] | x[3]) != 0;
+                } else {
 #pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        if (p == q) x[p] &= x[p] - 1;
+                    for (int q = 0; q < 4; ++q)
+                        for (; x[q] && !lose; x[q] &= x[q] - 1)
+                            lose = sh.t[(w0 + q) * 64 + __ffsll((unsigned long long)x[q]) - 1] == s.t;
                 }
             }
         }
@@ -217,9 +219,10 @@ __device__ __forceinline__ int32_t core_rounds(const Far &far, CoreShared &sh, C
         if (act) *mine = 0;
         if (wm) {
             if (lane == 0) atomicAdd(&sh.nwin, (int)__popcll(wm));
+            if (span == kCore && lane == 0) sh.won[w] = wm;  // the wavefront's own word
             if (win) {
-                atomicOr((unsigned long long *)&sh.won[rw], (unsigned long long)rbit);
-                atomicAdd(&sh.wdeg, (unsigned long long)s.deg);
+                if (span != kCore) atomicOr((unsigned long long *)&sh.won[rw], (unsigned long long)rbit);
+                if (degrees) atomicAdd(&sh.wdeg, (unsigned long long)s.deg);
                 commit(s, r);
             }
         }
@@ -448,7 +451,7 @@ __global__ __launch_bounds__(kCore) void k_core_rounds(D d, CoreMem cm) {
     __syncthreads();
     int64_t nodes = 0;
     const int32_t last = core_rounds(
-        CoreMaps<D>{d}, sh, s, r0, n, degsum, &nodes,
+        CoreMaps<D>{d}, sh, s, r0, n, true, degsum, &nodes,
         [&](const CoreState &x, int32_t r) {
             d.c[x.v] = x.t;
             if (d.grounds) atomicMax(&d.grounds[d.gidx[x.v]], r);

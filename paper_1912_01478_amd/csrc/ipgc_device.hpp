@@ -250,6 +250,34 @@ __device__ __forceinline__ MapRef map_of(const D &d, int32_t w, int64_t fsh) {
     return MapRef{(uint64_t)(a + w + fsh), (uint32_t)(e - a) + 1u};
 }
 
+// Row entries k .. k + 3 of the m entries at p, in one load (rows start at any entry: 4-byte alignment is all
+// that such a load needs); entries past the array's end read as `none`.  A lane's own row shares its cache
+// line with no other lane's, so each load costs a wavefront 64 line look-ups whatever its width.
+struct __attribute__((packed, aligned(4))) Entry4 {
+    int32_t x[4];
+};
+template <typename K>
+__device__ __forceinline__ void load4(const int32_t *p, K k, K m, int32_t none, int32_t (&u)[4]) {
+    if (k + 4 <= m) {
+        const Entry4 q = *reinterpret_cast<const Entry4 *>(p + k);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = q.x[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = k + j < m ? p[k + j] : none;
+    }
+}
+
+// Row bounds p[v], p[v + 1] in one load.
+template <typename Off>
+struct __attribute__((packed, aligned(sizeof(Off)))) Bounds {
+    Off b, e;
+};
+template <typename Off>
+__device__ __forceinline__ Bounds<Off> row_of(const Off *p, int64_t v) {
+    return *reinterpret_cast<const Bounds<Off> *>(p + v);
+}
+
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 __device__ __forceinline__ uint64_t lanes_below() {

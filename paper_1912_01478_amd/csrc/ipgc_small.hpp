@@ -14,7 +14,12 @@ namespace ipgc {
 
 // 14 bytes of shared memory a node: mask 8, color 2, two list entries 4.
 constexpr int kSmallNodes = 10240;
-constexpr int kSmallLight = 32;  // rows up to this length: a thread each; longer ones: 16 lanes or a wavefront
+// Rows up to this length take a thread each, longer ones 16 lanes or a wavefront.  A row stops at its first
+// conflict or its first larger id, so a lane reads a few entries of most rows, and 64 rows overlap in a
+// wavefront.  Whole calls at 32 / 64 / 128 / 256: uniform, 10^4 nodes of degree 32, 912 / 484 / 484 / 481 us;
+// of degree 64, 2391 / 1736 / 1165 / 1158; R-MAT, 8192 nodes and 2.0e5 entries, 616 / 615 / 564 / 568; 4096
+// nodes and 5.3e4 entries, 256 / 258 / 251 / 277.
+constexpr int kSmallLight = 128;
 
 struct SmallLists {
     uint64_t mask[kSmallNodes];     // bit t - 1: a committed neighbour has color t (t <= 64)
@@ -89,8 +94,8 @@ __device__ __forceinline__ int wave_append(bool flag, int *count) {
 }
 
 // One round's conflict tests, commits and pushes of the short rows, a lane each, two in flight per lane.
-__device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, const int32_t *ci, int32_t *out, int p,
-                                            bool sorted, bool deg) {
+__device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, const int32_t *ci, int32_t m, int32_t *out,
+                                            int p, bool sorted, bool deg) {
     constexpr int K = 2, C = 4;
     const int nl = sh.nl[p];
     const uint16_t *cur = sh.a.wl[p];
@@ -106,17 +111,21 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             t[j] = v[j] >= 0 ? -(int)sh.a.c[v[j]] : 0;
-            b[j] = v[j] >= 0 ? rp[v[j]] : 0;
-            e[j] = v[j] >= 0 ? rp[v[j] + 1] : 0;
+            const Bounds<int32_t> row = v[j] >= 0 ? row_of(rp, v[j]) : Bounds<int32_t>{0, 0};
+            b[j] = row.b;
+            e[j] = row.e;
             done |= (b[j] >= e[j] ? 1u : 0u) << j;
         }
         for (int q0 = 0; done != (1u << K) - 1; q0 += C) {
             int u[K][C];
 #pragma unroll
             for (int j = 0; j < K; ++j)
+            {
+                if (!(done >> j & 1u)) load4(ci, b[j] + q0, m, INT32_MAX, u[j]);
 #pragma unroll
                 for (int q = 0; q < C; ++q)
-                    u[j][q] = !(done >> j & 1u) && b[j] + q0 + q < e[j] ? ci[b[j] + q0 + q] : INT32_MAX;
+                    if ((done >> j & 1u) || b[j] + q0 + q >= e[j]) u[j][q] = INT32_MAX;
+            }
 #pragma unroll
             for (int j = 0; j < K; ++j) {
                 bool past = false;
@@ -144,11 +153,10 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
             const unsigned long long bit = 1ull << (t[j] - 1);
             for (int k = b[j]; k < e[j]; k += C) {
                 int u[C];
-#pragma unroll
-                for (int q = 0; q < C; ++q) u[q] = k + q < e[j] ? ci[k + q] : -1;
+                load4(ci, k, m, -1, u);
 #pragma unroll
                 for (int q = 0; q < C; ++q)
-                    if (u[q] >= 0) atomicOr((unsigned long long *)&sh.a.mask[u[q]], bit);
+                    if (k + q < e[j]) atomicOr((unsigned long long *)&sh.a.mask[u[q]], bit);
             }
         }
     }
@@ -310,7 +318,7 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
             if (tid == 0) sh.nl[p ^ 1] = sh.nw[p ^ 1] = 0;
             core_sync();
             small_wide(sh, rp, ci, out, p, sorted, keep);
-            small_light(sh, rp, ci, out, p, sorted, keep);
+            small_light(sh, rp, ci, (int32_t)m, out, p, sorted, keep);
             core_sync();
             p ^= 1;
             ++r;
@@ -383,11 +391,10 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
         else {
             for (int k = b; k < e; k += 4) {
                 int32_t u[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) u[q] = k + q < e ? ci[k + q] : -1;
+                load4(ci, k, (int32_t)m, -1, u);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (u[q] >= 0) put(tid, u[q]);
+                    if (k + q < e) put(tid, u[q]);
             }
         }
         int32_t *node = reinterpret_cast<int32_t *>(sh.core.bucket);  // node of each rank, until the rounds start
@@ -410,7 +417,7 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
     }
     int64_t nodes = 0;
     const int32_t last = core_rounds(
-        SmallRow{rp, ci, out}, sh.core, s, r, nact, deg, &nodes,
+        SmallRow{rp, ci, out}, sh.core, s, r, nact, keep, deg, &nodes,
         [&](const CoreState &x, int32_t) { out[x.v] = x.t; },
         [&](int32_t q, int32_t active, int64_t dsum) {
             if (keep && q - 1 < a.trace_cap) {
