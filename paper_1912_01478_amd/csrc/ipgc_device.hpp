@@ -1451,8 +1451,9 @@ __device__ __forceinline__ void light_assign(const D &d, const ClassView &cv, bo
     #pragma unroll
         for (int j = 0; j < K; ++j) {
             const bool a = act >> j & 1u;
-            b[j] = a ? d.rowptr[v[j]] : 0;
-            len[j] = a ? (int32_t)(d.rowptr[v[j] + 1] - b[j]) : 0;
+            const Bounds<Off> row = a ? row_of(d.rowptr, v[j]) : Bounds<Off>{0, 0};
+            b[j] = row.b;
+            len[j] = (int32_t)(row.e - row.b);
             gb[j] = a ? d.base(v[j]) : 0;
             used[j] = 0;
         }
@@ -1460,12 +1461,11 @@ __device__ __forceinline__ void light_assign(const D &d, const ClassView &cv, bo
             int32_t cu[K][C];
     #pragma unroll
             for (int j = 0; j < K; ++j)
-    #pragma unroll
-                for (int q = 0; q < C; ++q) cu[j][q] = q0 + q < len[j] ? d.colidx[b[j] + q0 + q] + gb[j] : -1;
+                if (q0 < len[j]) load4<int64_t>(d.colidx, (int64_t)b[j] + q0, d.m, 0, cu[j]);
     #pragma unroll
             for (int j = 0; j < K; ++j)
     #pragma unroll
-                for (int q = 0; q < C; ++q) cu[j][q] = cu[j][q] >= 0 ? d.c[cu[j][q]] : 0;
+                for (int q = 0; q < C; ++q) cu[j][q] = q0 + q < len[j] ? d.c[cu[j][q] + gb[j]] : 0;
             bool more = false;
     #pragma unroll
             for (int j = 0; j < K; ++j) {
@@ -1533,48 +1533,51 @@ __device__ __forceinline__ void light_conflict(const D &d, const ClassView &cv, 
         Off b[K];
         int32_t len[K], gb[K];
         uint32_t pm[K];  // pull-only: unused; push modes: pending positions not yet scanned
-    #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const bool a = act >> j & 1u;
-            b[j] = a ? d.rowptr[v[j]] : 0;
-            len[j] = a ? (int32_t)(d.rowptr[v[j] + 1] - b[j]) : 0;
-            gb[j] = a ? d.base(v[j]) : 0;
-            pm[j] = a && !pull_only ? d.pend[v[j]] : 0u;
-        }
         uint32_t lose = 0, done = ~act;  // bit j
         uint32_t seen[K];                // push modes: positions found committed
         int32_t read = 0;
     #pragma unroll
-        for (int j = 0; j < K; ++j) seen[j] = 0;
-        for (int32_t q0 = 0;; q0 += C) {
-            int32_t pos[K][C], u[K][C];
+        for (int j = 0; j < K; ++j) {
+            const bool a = act >> j & 1u;
+            const Bounds<Off> row = a ? row_of(d.rowptr, v[j]) : Bounds<Off>{0, 0};
+            b[j] = row.b;
+            len[j] = (int32_t)(row.e - row.b);
+            gb[j] = a ? d.base(v[j]) : 0;
+            pm[j] = a && !pull_only ? d.pend[v[j]] : 0u;
+            seen[j] = 0;
+        }
+    #pragma unroll
+        for (int j = 0; j < K; ++j)
+            if (pull_only ? len[j] == 0 : pm[j] == 0) done |= 1u << j;
+        // C entries of each row at a time: the next ones, or the next aligned C with a pending position
+        for (int32_t q0 = 0; (done & ((1u << K) - 1)) != (1u << K) - 1; q0 += C) {
+            int32_t k[K], u[K][C];
+            uint32_t ok[K];  // bit q: entry k + q is scanned
+    #pragma unroll
+            for (int j = 0; j < K; ++j) {
+                k[j] = pull_only ? q0 : pm[j] ? (__ffs(pm[j]) - 1) & ~(C - 1) : 0;
+                ok[j] = pull_only ? (len[j] - q0 >= C ? 0xFu : (1u << max(len[j] - q0, 0)) - 1u) : pm[j] >> k[j] & 0xFu;
+                pm[j] &= ~(0xFu << k[j]);
+                if (done >> j & 1u) ok[j] = 0;
+            }
     #pragma unroll
             for (int j = 0; j < K; ++j)
-    #pragma unroll
-                for (int q = 0; q < C; ++q) {
-                    if (pull_only) {
-                        pos[j][q] = !(done >> j & 1u) && q0 + q < len[j] ? q0 + q : -1;
-                    } else {
-                        pos[j][q] = !(done >> j & 1u) && pm[j] ? __ffs(pm[j]) - 1 : -1;
-                        pm[j] &= pm[j] - 1;
-                    }
-                }
-    #pragma unroll
-            for (int j = 0; j < K; ++j)
-    #pragma unroll
-                for (int q = 0; q < C; ++q) u[j][q] = pos[j][q] >= 0 ? d.colidx[b[j] + pos[j][q]] + gb[j] : INT32_MAX;
+                if (ok[j]) load4<int64_t>(d.colidx, (int64_t)b[j] + k[j], d.m, 0, u[j]);
             int32_t cu[K][C];
     #pragma unroll
             for (int j = 0; j < K; ++j)
     #pragma unroll
-                for (int q = 0; q < C; ++q) cu[j][q] = u[j][q] < v[j] ? d.c[u[j][q]] : 0;
+                for (int q = 0; q < C; ++q) {
+                    u[j][q] = ok[j] >> q & 1u ? u[j][q] + gb[j] : INT32_MAX;
+                    cu[j][q] = u[j][q] < v[j] ? d.c[u[j][q]] : 0;
+                }
     #pragma unroll
             for (int j = 0; j < K; ++j) {
     #pragma unroll
                 for (int q = 0; q < C; ++q) {
-                    if (done >> j & 1u) continue;
-                    if (u[j][q] >= v[j]) {  // not a smaller neighbour; past the row's end if INT32_MAX
-                        if (d.sorted || u[j][q] == INT32_MAX) done |= 1u << j;
+                    if ((done >> j & 1u) || !(ok[j] >> q & 1u)) continue;
+                    if (u[j][q] >= v[j]) {  // not a smaller neighbour
+                        if (d.sorted) done |= 1u << j;
                         continue;
                     }
                     ++read;
@@ -1582,11 +1585,10 @@ __device__ __forceinline__ void light_conflict(const D &d, const ClassView &cv, 
                         lose |= 1u << j;
                         done |= 1u << j;
                     }
-                    if (cu[j][q] > 0) seen[j] |= 1u << pos[j][q];
+                    if (cu[j][q] > 0) seen[j] |= 1u << (k[j] + q);
                 }
                 if (pull_only ? q0 + C >= len[j] : pm[j] == 0) done |= 1u << j;
             }
-            if ((done & ((1u << K) - 1)) == (1u << K) - 1) break;
         }
         if (!pull_only) {
     #pragma unroll
@@ -1642,10 +1644,12 @@ __device__ __forceinline__ void light_conflict(const D &d, const ClassView &cv, 
             for (int32_t q0 = 0;; q0 += C) {
                 int32_t w[K][C];
     #pragma unroll
-                for (int j = 0; j < K; ++j)
+                for (int j = 0; j < K; ++j) {
+                    const bool a = (win >> j & 1u) && q0 < len[j];
+                    if (a) load4<int64_t>(d.colidx, (int64_t)b[j] + q0, d.m, 0, w[j]);
     #pragma unroll
-                    for (int q = 0; q < C; ++q)
-                        w[j][q] = (win >> j & 1u) && q0 + q < len[j] ? d.colidx[b[j] + q0 + q] + gb[j] : -1;
+                    for (int q = 0; q < C; ++q) w[j][q] = a && q0 + q < len[j] ? w[j][q] + gb[j] : -1;
+                }
                 uint64_t mw[K][C];
     #pragma unroll
                 for (int j = 0; j < K; ++j)
