@@ -102,8 +102,7 @@ struct Workspace {
     DBuf<int32_t> static_list, seg_list0, seg_list1, seg_cnt, block_cnt, hub_pre, hub_cnt, trace, lstart, llen, lower;
     DBuf<HubRec> hub_won;
     DBuf<int64_t> seg_deg, block_deg, units, trace_deg;
-    DBuf<int8_t> cls;
-    DBuf<uint8_t> F;
+    DBuf<uint8_t> tag, F;
     DBuf<uint64_t> mask;
     DBuf<uint32_t> pend;
     DBuf<int64_t> growptr, node_off, edge_off;  // batches: union row starts, graph offsets
@@ -148,7 +147,7 @@ struct Workspace {
         TRY(f(units, (int64_t)kNumUnits * kMaxRoundBlocks));
         TRY(f(trace, n));
         TRY(f(trace_deg, n));
-        TRY(f(cls, n));
+        TRY(f(tag, n));
         TRY(f(F, m + n + 64));
         TRY(f(mask, n));
         TRY(f(pend, n));
@@ -206,7 +205,7 @@ struct Workspace {
         static_list.release(); seg_list0.release(); seg_list1.release(); seg_cnt.release(); hub_won.release();
         hub_pre.release(); hub_cnt.release();
         block_cnt.release(); trace.release(); lstart.release(); llen.release(); lower.release();
-        seg_deg.release(); block_deg.release(); units.release(); trace_deg.release(); cls.release();
+        seg_deg.release(); block_deg.release(); units.release(); trace_deg.release(); tag.release();
         F.release(); mask.release(); pend.release(); ticks.release(); bar.release(); growptr.release(); node_off.release(); edge_off.release();
         gbase.release(); gidx.release(); grounds.release(); ctb.release(); sorted_rows.release();
         gthr.release(); gleft.release(); trace_topo.release(); gsplit.release();
@@ -501,7 +500,7 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
 
     const int64_t H = schedule_threshold(P, n_here);
 
-    d.cls = ws.cls.p;
+    d.tag = ws.tag.p;
     d.F = ws.F.p;
     d.mask = ws.mask.p;
     d.pend = ws.pend.p;
@@ -546,7 +545,7 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
     TRY(clear(ws.bar.p, sizeof(Barrier), s));
     TRY(clear(ws.units.p, sizeof(int64_t) * kNumUnits * grid, s));
     TRY(pf.begin(kKindInit));
-    k_init<<<prep_grid, kPrepBlock, 0, s>>>(d, ws.cls.p, (int32_t)span, P.check_ids ? 1 : 0);
+    k_init<<<prep_grid, kPrepBlock, 0, s>>>(d, (int32_t)span, P.check_ids ? 1 : 0);
     k_offsets<<<1, 1024, 0, s>>>(d, prep_grid);
     k_fill_static<<<prep_grid, kPrepBlock, 0, s>>>(d, (int32_t)span, P.light);
     TRY(pf.end(kKindInit));
@@ -847,6 +846,7 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
         d.gidx = ws.gidx.p;
         d.gend = ws.node_off.p + 1;
         d.grounds = ws.grounds.p;
+        d.parts = graphs - (int64_t)small.size() >= kPartsGraphs && grid >= 64 && grid % kXcds == 0;
         d.c = out_colors_packed;
     };
     // a workgroup's out segment per class holds (its share + a workgroup) entries, twice that with

@@ -332,8 +332,8 @@ __global__ __launch_bounds__(kCore) void k_core_build(D d, CoreMem cm) {
     __syncthreads();
     const int32_t v = cm.node[i].v;
     const int64_t b = d.rowptr[v], deg = d.rowptr[v + 1] - b;
-    const int32_t t = max(1, -d.c[v]);
-    const bool light = d.cls[v] == kL;
+    const int32_t t = max(1, -state_of(d, v));
+    const bool light = deg <= d.light_max;
     const int32_t start = light ? 0 : d.lstart[v], len = light ? (int32_t)deg : d.llen[v];
     const int32_t gb = light ? d.base(v) : 0;  // rows hold ids local to the graph, rings global ones
     const bool pull = light && d.light_pull != kPushAll;
@@ -349,16 +349,17 @@ __global__ __launch_bounds__(kCore) void k_core_build(D d, CoreMem cm) {
             u[j] = k < len ? list[b + p] + gb : -1;
         }
 #pragma unroll
-        for (int j = 0; j < P; ++j) cu[j] = u[j] >= 0 ? d.c[u[j]] : 1;
+        for (int j = 0; j < P; ++j) cu[j] = u[j] >= 0 ? d.tag[u[j]] : 0;
 #pragma unroll
         for (int j = 0; j < P; ++j) {
             if (u[j] < 0) continue;
-            if (cu[j] <= 0) {
+            if (!(cu[j] & kDone)) {
                 if (u[j] >= v) continue;
                 const int q = cm.rank[u[j]];
                 atomicOr((unsigned long long *)&row[q >> 6], 1ull << (q & 63));
-            } else if (pull && cu[j] >= t && cu[j] < t + 128) {
-                atomicOr((unsigned long long *)&win[(cu[j] - t) >> 6], 1ull << ((cu[j] - t) & 63));
+            } else if (pull) {  // a node of class L needs no color above 33
+                const int32_t x = (cu[j] & kTagMax) - t;
+                if (x >= 0 && x < 64) atomicOr((unsigned long long *)&win[0], 1ull << x);
             }
         }
     }

@@ -16,6 +16,7 @@ namespace ipgc {
 
 constexpr int kDefaultLightMax = 32;
 constexpr int kDefaultHubMin = 1024;
+constexpr int kPartsGraphs = 64;        // graphs of a union from which its parts stay on one XCD each (8 a part)
 constexpr int kDefaultTailGroups = 32;  // workgroups kept for small data-driven rounds (0: all)
 
 // Message of the last failing call on this thread (ipgc_last_error).

@@ -62,7 +62,7 @@ struct AdmitJob {
 };
 
 __global__ __launch_bounds__(256) void k_srv_admit(AdmitJob j, int32_t light_max, int32_t hub_min, int64_t *growptr,
-                                                   int32_t *gbase, int32_t *gidx, int8_t *cls, int32_t *c, uint64_t *mask,
+                                                   int32_t *gbase, int32_t *gidx, int8_t *cls, uint8_t *tag, uint64_t *mask,
                                                    uint32_t *pend,
                                                    int32_t *lstart, int32_t *llen, int64_t *gend, int64_t *gfshift,
                                                    int32_t *gleft, int32_t *grounds, int32_t *gerr) {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void k_srv_admit(AdmitJob j, int32_t light_max
             bad |= a != m;
             growptr[v] = e0 + m;
             cls[v] = kNoNode;
-            c[v] = 1;
+            tag[v] = kDone;
             continue;
         }
         const int64_t e = rp[lv + 1];
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void k_srv_admit(AdmitJob j, int32_t light_max
         const int64_t dv = ok ? e - a : 0;
         cls[v] = (int8_t)node_class(dv, light_max, hub_min);
         if (cls[v] == kL) pend[v] = dv >= 32 ? ~0u : (1u << dv) - 1u;
-        c[v] = 0;
+        tag[v] = 0;
     }
     if (__ballot(bad) && lane_id() == 0) gerr[slot] = 1;
 }
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kSrvBlock) void k_srv_scan(SDev d, int64_t nhigh, i
     for (int64_t c0 = lo; c0 < hi; c0 += blockDim.x) {
         const int64_t v = c0 + threadIdx.x;
         const int k = v < hi ? d.cls[v] : kNoNode;
-        const bool act = k >= 0 && d.c[v] <= 0;
+        const bool act = k >= 0 && !(d.tag[v] & kDone);
         const int64_t deg = act ? d.rowptr[v + 1] - d.rowptr[v] : 0;
         for (int q = 0; q < kNumClasses; ++q) {
             const uint64_t live = __ballot(k == q);
@@ -296,7 +296,7 @@ struct Server {
     DBuf<uint32_t> pend;
     DBuf<int32_t> grounds, gleft, gerr;
     DBuf<int8_t> cls;
-    DBuf<uint8_t> F;
+    DBuf<uint8_t> F, tag;
     DBuf<HubRec> hub_won;
     DBuf<Barrier> bar;
     DBuf<Counters> ctb;
@@ -368,6 +368,7 @@ int Server::create(const ipgc_server_config &cfg) {
     TRY(gbase.reserve(ncap));
     TRY(gidx.reserve(ncap));
     TRY(c.reserve(ncap));
+    TRY(tag.reserve(ncap));
     TRY(mask.reserve(ncap));
     TRY(pend.reserve(ncap));
     TRY(cls.reserve(ncap));
@@ -417,7 +418,7 @@ int Server::create(const ipgc_server_config &cfg) {
     h_gleft.assign(max_jobs, 0);
     h_grounds.assign(max_jobs, 0);
     h_gerr.assign(max_jobs, 0);
-    st.arena_bytes = (int64_t)(sizeof(int64_t) * (ncap + 1) + sizeof(int32_t) * ncap * 7 + ncap +
+    st.arena_bytes = (int64_t)(sizeof(int64_t) * (ncap + 1) + sizeof(int32_t) * ncap * 7 + 2 * ncap +
                                sizeof(int32_t) * (ncap + 1) + sizeof(int32_t) * 2 * std::max<int64_t>(ecap, 1) +
                                fcap + 2 * kFPad + sizeof(int32_t) * 2 * seg + sizeof(HubRec) * hubs);
     return IPGC_OK;
@@ -428,7 +429,7 @@ void Server::destroy() {
     colidx.release(); gbase.release(); gidx.release(); c.release(); lower.release(); lstart.release();
     llen.release(); static_list.release(); seg0.release(); seg1.release(); seg_cnt.release();
     block_cnt.release(); stage.release(); grounds.release(); gleft.release(); gerr.release(); cls.release();
-    F.release(); mask.release(); pend.release(); hub_won.release(); bar.release(); ctb.release();
+    F.release(); tag.release(); mask.release(); pend.release(); hub_won.release(); bar.release(); ctb.release();
     if (host_ct) (void)hipHostFree(host_ct);
     if (s) (void)hipStreamDestroy(s);
     if (cs) (void)hipStreamDestroy(cs);
@@ -450,6 +451,7 @@ SDev Server::dev_view(int64_t nhigh, int64_t threshold) {
     d.gleft = gleft.p;
     d.gfshift = gfshift.p;
     d.c = c.p;
+    d.tag = tag.p;
     d.cls = cls.p;
     d.F = F.p + kFPad;
     d.mask = mask.p;
@@ -486,6 +488,7 @@ SDev Server::dev_view(int64_t nhigh, int64_t threshold) {
     d.racy = P.racy ? 1 : 0;
     d.tail_groups = P.tail_groups;
     d.discard = P.mode == IPGC_MODE_REBUILD ? 1 : 0;
+    d.parts = st.resident >= kPartsGraphs && grid >= 64 && grid % kXcds == 0;
     d.bar_limit = bar_limit;
     return d;
 }
@@ -581,7 +584,7 @@ int Server::admit_staged() {
         const int64_t v0 = j.v0, e0 = j.e0, f0 = j.f0;
         const AdmitJob aj{stage.p + j.stage, j.n, j.m, e0, f0 - (e0 + v0), (int32_t)v0, slot, j.r_adm};
         const int blocks = (int)std::min<int64_t>(4096, (j.n + 1 + 255) / 256);
-        k_srv_admit<<<blocks, 256, 0, s>>>(aj, P.light_max, P.hub_min, growptr.p, gbase.p, gidx.p, cls.p, c.p, mask.p, pend.p,
+        k_srv_admit<<<blocks, 256, 0, s>>>(aj, P.light_max, P.hub_min, growptr.p, gbase.p, gidx.p, cls.p, tag.p, mask.p, pend.p,
                                            lstart.p, llen.p, gend.p, gfshift.p, gleft.p, grounds.p, gerr.p);
         SDev d = dev_view(nodes.high(), 0);
         const int pblocks = (int)std::min<int64_t>(8192, (j.n + 3) / 4);
