@@ -1966,8 +1966,12 @@ __device__ __forceinline__ void push_row_wave(const D &d, int64_t b, int64_t e, 
 // S = 64 or 16 lanes (a wavefront, or a quarter of one) scan node v's ring; the
 // lanes of the group agree on every loop condition, and ballots are masked to
 // the group.  Quarter-wave groups read four chunks of 16 entries per pass.
+//
+// At most `passes` passes over the first `limit` entries; *left: how many of those it has not read (0 if it found a
+// conflict), which are then the ring's first ones.
 template <class D>
-__device__ __forceinline__ bool ring_scan_group(const D &d, int32_t v, int32_t t, int wide, int S, Units &un) {
+__device__ __forceinline__ bool ring_scan_group(const D &d, int32_t v, int32_t t, int wide, int S, Units &un, int32_t limit,
+                                                int passes, int first_chunks, int32_t *left) {
     constexpr int kPass = 4;
     const int lane = lane_id(), gl = lane % S;
     const uint64_t gm = S == kWave ? ~0ull : (((1ull << S) - 1) << (lane - gl));
@@ -1976,14 +1980,15 @@ __device__ __forceinline__ bool ring_scan_group(const D &d, int32_t v, int32_t t
     int32_t start = d.lstart[v], len = d.llen[v];
     int32_t read = 0, kept = 0;
     bool lose = false;
-    int chunks = S == kWave ? 1 : kPass;  // a wavefront's first pass reads one chunk (a loser often stops there)
-    while (read < len && !lose) {
+    int chunks = S == kWave ? first_chunks : kPass;  // a wavefront's first pass reads one chunk (a loser often stops there)
+    limit = min(limit, len);
+    for (int ps = 0; ps < passes && read < limit && !lose; ++ps) {
         int32_t u[kPass], cu[kPass];
 #pragma unroll
         for (int j = 0; j < kPass; ++j) {
             const int32_t k = read + j * S + gl;
             u[j] = -1;
-            if (j < chunks && k < len) {
+            if (j < chunks && k < limit) {
                 int32_t p = start + k;
                 if (p >= cap) p -= cap;
                 u[j] = d.lower[base + p];
@@ -2005,7 +2010,7 @@ __device__ __forceinline__ bool ring_scan_group(const D &d, int32_t v, int32_t t
             kept += __popcll(km);
         }
         lose = (__ballot(hit) & gm) != 0;
-        read += min(chunks * S, len - read);
+        read += min(chunks * S, limit - read);
         if (S == kWave) chunks = wide;
     }
     un.u[kUConflictEntries] += gl == 0 ? read : 0;
@@ -2016,6 +2021,7 @@ __device__ __forceinline__ bool ring_scan_group(const D &d, int32_t v, int32_t t
         d.lstart[v] = s2;
         d.llen[v] = len - read + kept;
     }
+    *left = lose ? 0 : limit - read;
     return lose;
 }
 
@@ -2141,7 +2147,8 @@ __device__ __forceinline__ void wide_conflict_item(const D &d, const RoundIn &in
                                                    const int64_t (&seg_base)[kNumClasses], int *s_cnt,
                                                    unsigned long long *s_deg) {
     const int32_t t = -cv;
-    const bool lose = ring_scan_group(d, v, t, in.total <= kWideScanMax ? 4 : 1, S, un);
+    int32_t left;
+    const bool lose = ring_scan_group(d, v, t, in.total <= kWideScanMax ? 4 : 1, S, un, INT32_MAX, INT32_MAX, 1, &left);
     const int64_t b = d.rowptr[v], e = d.rowptr[v + 1];
     const int q = hub ? kM : kW;
     if (gl == 0) un.u[kUConflictNodes] += 1;
@@ -2166,12 +2173,15 @@ __device__ __forceinline__ void wide_conflict_item(const D &d, const RoundIn &in
     }
 }
 
+constexpr int kGroupPasses = 2;  // passes of a ring by a group of 8 or 16 lanes, before the wavefront takes over
+
 // part: 0 the round's only pass; 1 and 2 the two passes of a round of both kinds (per-graph
 // schedules), whose losers share the workgroup's out segments: the first clears the counts, the
 // second writes them.
 template <class D>
 __device__ __forceinline__ void conflict_step(const D &d, const RoundIn &in, const OutSegs &os, int32_t r, Units &un, int G,
                                               int part = 0) {
+    using Off = typename D::OffT;
     const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (int64_t)G * blockDim.x;
     const int64_t gw = gt / kWave, nw = nt / kWave;
     const int lane = lane_id();
@@ -2232,16 +2242,72 @@ __device__ __forceinline__ void conflict_step(const D &d, const RoundIn &in, con
                 continue;
             }
         }
-        // the loop is the same for the whole wavefront; group lane / S takes item i0 + lane / S
+        // The loop is the same for the whole wavefront; group lane / S takes item i0 + lane / S.  A group scans
+        // at most kGroupPasses passes of its ring; what is left of the rings goes to the whole wavefront, one
+        // after another, and so do the rows of the winners.  Most nodes lose early, but the longest rows
+        // otherwise held their 8 lanes for 32 passes of the ring and 32 of the row, 165 us a round on R-MAT
+        // graphs however many nodes it had.
         const Walk wk(d, hi - lo, per, G, true, false);
         for (int64_t i0 = lo + wk.first; i0 < lo + wk.end; i0 += wk.step) {
             const int64_t i = i0 + lane / S;
-            if (i >= lo + wk.end) continue;
             const bool hub = i >= nW;
-            const int32_t v = hub ? in.cv[kM].at((int32_t)(i - nW)) : in.cv[kW].at((int32_t)i);
-            const int32_t cv = state_of(d, v);
-            if (skip_item(d, in, v, cv)) continue;
-            wide_conflict_item(d, in, os, r, un, v, cv, hub, S, gl, discard, seg_base, s_cnt, s_deg);
+            int32_t v = 0, cv = 1;
+            bool has = false;
+            if (i < lo + wk.end) {
+                v = hub ? in.cv[kM].at((int32_t)(i - nW)) : in.cv[kW].at((int32_t)i);
+                cv = state_of(d, v);
+                has = !skip_item(d, in, v, cv);
+            }
+            bool lose = false, on = has;
+            int32_t rest = 0, x = v, xt = -cv, limit = INT32_MAX;
+            int xs = S, src = 0;
+            uint64_t um = 0;
+            for (bool first = true;; first = false) {  // the groups' own passes, then a ring at a time
+                bool l = false;
+                int32_t left = 0;
+                if (on)
+                    l = ring_scan_group(d, x, xt, in.total <= kWideScanMax ? 4 : 1, xs, un, limit,
+                                        first && S < kWave ? kGroupPasses : INT32_MAX, first ? 1 : 4, &left);
+                if (first) {
+                    lose = l;
+                    rest = left;
+                    um = __ballot(has && !l && left > 0 && gl == 0);
+                } else if (lane / S == src / S) {
+                    lose = l;
+                }
+                if (!um) break;
+                src = __ffsll((unsigned long long)um) - 1;
+                um &= um - 1;
+                x = __shfl(v, src);
+                xt = -__shfl(cv, src);
+                limit = __shfl(rest, src);
+                xs = kWave;
+                on = true;
+            }
+            const bool lead = has && gl == 0;
+            const Bounds<Off> row = lead ? row_of(d.rowptr, v) : Bounds<Off>{0, 0};
+            if (lead) {
+                un.u[kUConflictNodes] += 1;
+                const int q = hub ? kM : kW;
+                if (lose) {
+                    if (d.racy) d.tag[v] = 0;
+                    const int p = atomicAdd(&s_cnt[q], 1);
+                    atomicAdd(&s_deg[q], (unsigned long long)(row.e - row.b));
+                    if (!discard) os.list[seg_base[q] + p] = v;
+                } else {
+                    commit_color(d, v, -cv);
+                    un.u[kUCommits] += 1;
+                    if (d.grounds) commits_graph(d, d.gidx[v], 1, r);
+                    if (hub) commits_hub(d, v);
+                    else un.u[kUPushEntries] += (uint32_t)(row.e - row.b);
+                }
+            }
+            for (uint64_t wm = __ballot(lead && !lose && !hub); wm; wm &= wm - 1) {  // the winners' rows
+                const int src2 = __ffsll((unsigned long long)wm) - 1;
+                const int32_t w = __shfl(v, src2);
+                const int64_t b = __shfl((long long)row.b, src2), e = __shfl((long long)row.e, src2);
+                push_row_wave(d, b, e, -__shfl(cv, src2), d.base(w), d.fshift(w));
+            }
         }
     }
     // class L: a lane per node, several nodes in flight per lane
