@@ -122,7 +122,8 @@ typedef struct ipgc_options {
                                   each (1..32; 0: default 32) */
     int32_t hub_min_degree;    /* nodes with degree above this are hubs: when one commits, the whole
                                   grid writes its color into its neighbours' byte maps in a separate
-                                  step of the round (> light_max_degree; 0: default 1024) */
+                                  step of the round (> light_max_degree; 0: 512 for graphs of more than
+                                  2^23 entries, else 2048; a server: 1024) */
     int32_t validate;          /* IPGC_VALIDATE_* */
     int32_t flags;             /* IPGC_FLAG_* */
     ipgc_profile *profile;     /* optional per-kernel timing and work counts (NULL: none) */

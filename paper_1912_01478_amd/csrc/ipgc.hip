@@ -295,6 +295,7 @@ int parse_options(const ipgc_options *opt, int mode, Params *p) {
     if (opt) o = *opt;
     p->mode = mode;
     p->light_max = o.light_max_degree ? o.light_max_degree : kDefaultLightMax;
+    p->hub_auto = !o.hub_min_degree;
     p->hub_min = o.hub_min_degree ? o.hub_min_degree : std::max(kDefaultHubMin, p->light_max + 1);
     if (p->light_max < 1 || p->light_max > kLightMaxLimit)
         return fail(IPGC_EINVAL, "light_max_degree %d outside 1..%d", p->light_max, kLightMaxLimit);
@@ -391,6 +392,15 @@ int round_grid(Workspace &ws, int dev, const Params &P, int64_t n, int64_t m, bo
     return IPGC_OK;
 }
 
+// Default W/M cut-off.  A W node is scanned and pushed by one wavefront, so in large graphs the longest W rows
+// set the length of a round: hand them to the whole grid from 512 entries on.  In small ones the push step of
+// class M costs a round an extra barrier, and is left to fewer rounds.  Whole calls at 512 / 1024 / 2048: R-MAT of
+// 2^22 nodes (1.3e8 entries) 16.8 / 18.4 / 18.5 ms, of 2^20 (1.6e7) 4.99 / 5.20 / 5.51, of 524 288 (1.6e7) 5.61 /
+// 5.86 / 5.86, of 300 007 (4.5e6) 2.94 / 2.94 / 2.88, of 65 536 (1.8e6) 2.10 / 1.97 / 1.86.
+int default_hub_min(const Params &P, int64_t m) {
+    return std::max(m > (1 << 23) ? 512 : 2048, P.light_max + 1);
+}
+
 // Preparation kernels: workgroup b covers nodes [b * span, (b + 1) * span).
 void prep_layout(int64_t n, int64_t *span, int *prep_grid) {
     *span = std::max<int64_t>(kPrepSpanMin, (n + kMaxPrepBlocks - 1) / kMaxPrepBlocks);
@@ -402,12 +412,16 @@ void prep_layout(int64_t n, int64_t *span, int *prep_grid) {
 // repeated ids and missing reverse entries.
 template <class D>
 int check_full(Workspace &ws, hipStream_t s, const D &d, int64_t n, int64_t m) {
-    TRY(ws.sorted_rows.reserve(std::max<int64_t>(m, 1)));  // in the plan when full validation is on
     TRY(clear(&ws.ct->bad_full, sizeof(int32_t), s));
-    const int sort_grid = (int)std::min<int64_t>(n, 65536);
-    k_full_sort<<<sort_grid, kSortBlock, 0, s>>>(d, 0, n, ws.sorted_rows.p, nullptr);
-    k_full_check<<<(int)std::min<int64_t>(16384, (n + 3) / 4), kPrepBlock, 0, s>>>(d, 0, n, ws.sorted_rows.p,
-                                                                                   &ws.ct->bad_full, nullptr);
+    const int32_t *rows = d.colidx;
+    if (!d.sorted) {  // rows already ascending are searched where they are
+        TRY(ws.sorted_rows.reserve(std::max<int64_t>(m, 1)));  // in the plan when full validation is on
+        const int sort_grid = (int)std::min<int64_t>(n, 65536);
+        k_full_sort<<<sort_grid, kSortBlock, 0, s>>>(d, 0, n, ws.sorted_rows.p, nullptr);
+        rows = ws.sorted_rows.p;
+    }
+    k_full_check<<<(int)std::max<int64_t>(1, std::min<int64_t>(16384, (m + kPrepBlock - 1) / kPrepBlock)), kPrepBlock, 0, s>>>(
+        d, 0, n, rows, &ws.ct->bad_full, nullptr);
     HIP_TRY(hipGetLastError());
     TRY(read_counters(ws, s));
     return full_check_verdict(ws.host_ct->bad_full);
@@ -565,8 +579,8 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
         const int64_t n_w = ws.host_ct->class_n[kW], n_hub = ws.host_ct->class_n[kM];
         const int64_t hub_chunks = ws.host_ct->hub_chunks;
         TRY(pf.begin(kKindPrep));
-        // a wavefront per W node, or a quarter wavefront per node while their rows hold at most 1024 entries
-        const int64_t per_wave = P.hub_min <= 1024 ? 4 : 1;
+        // a wavefront per W node, or a quarter wavefront per node while their rows hold at most 2048 entries
+        const int64_t per_wave = P.hub_min <= 2048 ? 4 : 1;
         if (n_w > 0)
             k_prep_wide<<<(int)std::min<int64_t>(8192, (n_w + 4 * per_wave - 1) / (4 * per_wave)), kPrepBlock, 0, s>>>(d);
         if (n_hub > 0) {
@@ -734,6 +748,7 @@ int color_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t 
     }
 
     // rowptr[0] == 0 and rowptr[n] == m are checked by k_init, before any row is read
+    if (P.hub_auto) P.hub_min = default_hub_min(P, m);
     int grid = 1, coop = 0;
     TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
     DevT<int32_t> d{};
@@ -833,10 +848,11 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
     TRY(ws.growptr.reserve(n + 1));
     TRY(ws.gbase.reserve(n));
     TRY(ws.gidx.reserve(n));
-    k_batch_union<<<(int)std::min<int64_t>(graphs, 16384), kPrepBlock, 0, s>>>(
+    k_batch_union<<<(int)std::min<int64_t>(8192, (std::max(n, graphs) + kPrepBlock - 1) / kPrepBlock), kPrepBlock, 0, s>>>(
         ws.node_off.p, ws.edge_off.p, rowptr_packed, graphs, small.empty() ? -1 : kSmallNodes, kSmallEntries, ws.growptr.p, ws.gbase.p, ws.gidx.p, ws.ct);
     HIP_TRY(hipGetLastError());
 
+    if (P.hub_auto) P.hub_min = default_hub_min(P, m_union);
     int grid = 1, coop = 0;
     TRY(round_grid(ws, dev, P, n_union, m_union, false, &grid, &coop));
     auto setup = [&](auto &d) {
@@ -957,10 +973,13 @@ int color_noalloc_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, 
     int prep_grid = 0;
     prep_layout(n, &span, &prep_grid);
     size_t used = 0;
-    // every workgroup takes 25 KiB of scratch: a graph near the scratch's end gets fewer
+    // every workgroup takes 25 KiB of scratch: a graph near the scratch's end gets fewer, and fewer hubs
+    const int hub_min = P.hub_min;
+    if (P.hub_auto) P.hub_min = default_hub_min(P, m);
     TRY(round_grid(ws, dev, P, n, m, false, &grid, &coop));
     int rc = ws.carve(base, kStaticScratchBytes, n, m, grid, prep_grid, P.hub_min, P.full, &used);
     if (rc == IPGC_ETOOBIG) {
+        P.hub_min = hub_min;
         TRY(round_grid(ws, dev, P, n, m, true, &grid, &coop));
         rc = ws.carve(base, kStaticScratchBytes, n, m, grid, prep_grid, P.hub_min, P.full, &used);
     }

@@ -798,7 +798,7 @@ __device__ void ring_build_wave(const D &d, int32_t v, int64_t lo, int64_t hi, i
 }
 
 // The same ring and checks for four W nodes at once, a quarter wavefront (16 lanes) each, for rows
-// of at most 1024 entries, where a wavefront per node would leave most of its lanes idle.  The
+// of at most 2048 entries, where a wavefront per node would leave most of its lanes idle.  The
 // pass loop runs for the longest of the four rows; has: this quarter holds a node.
 template <class D>
 __device__ __forceinline__ void ring_build_quarter(const D &d, int32_t v, bool has, int &bad, int &unsorted) {
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(kPrepBlock) void k_prep_wide(D d) {
     const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
     const int32_t nWide = d.ct->class_n[kW] + (d.hub_pre ? 0 : d.ct->class_n[kM]);
     int bad = 0, unsorted = 0;
-    if (d.hub_pre && d.hub_min <= 1024) {  // only class W here, rows of at most 1024 entries
+    if (d.hub_pre && d.hub_min <= 2048) {  // only class W here, rows of at most 2048 entries
         const int grp = lane_id() / 16;
         for (int64_t i0 = gw * 4; i0 < nWide; i0 += nw * 4) {  // the same for the whole wavefront
             const int64_t i = i0 + grp;
@@ -1024,71 +1024,96 @@ __global__ __launch_bounds__(kSortBlock) void k_full_sort(D d, int64_t v_lo, int
     }
 }
 
-// Checks of nodes [v_lo, v_hi) on the sorted rows (a wavefront per node); the
-// kFull* bits found are ORed into *flag.  Ids outside the node's graph are left
-// to the range checks (and never used as an index here).
+// The last node v in [lo, hi) with rowptr[v] <= k (rowptr[lo] <= k is assumed), by the whole wavefront: 64 row
+// pointers a step.
+template <class D>
+__device__ __forceinline__ int64_t row_owner(const D &d, int64_t lo, int64_t hi, int64_t k) {
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave, v = lo + lane_id() * step;
+        const uint64_t le = __ballot(v < hi && d.rowptr[v] <= k);
+        lo += (int64_t)(63 - __clzll((unsigned long long)le)) * step;
+        hi = min(hi, lo + step);
+    }
+    return lo;
+}
+
+// Checks of nodes [v_lo, v_hi) on the sorted rows; the kFull* bits found are ORed into *flag.  Ids outside the
+// node's graph are left to the range checks (and never used as an index here).  A wavefront takes 64
+// consecutive entries, whatever rows they lie in: a wavefront per node spent most of its time on the few longest
+// rows (R-MAT, 3e5 nodes and 4.5e6 entries: 1.08 ms).
 template <class D>
 __global__ __launch_bounds__(kPrepBlock) void k_full_check(D d, int64_t v_lo, int64_t v_hi, const int32_t *rows,
-                                                           int32_t *flag, const int32_t *skip) {
+                                                            int32_t *flag, const int32_t *skip) {
     if (skip && *skip) return;
     const int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nw = (int64_t)gridDim.x * blockDim.x / kWave;
     const int lane = lane_id();
+    const int64_t e_lo = d.rowptr[v_lo], e_hi = d.rowptr[v_hi];
     int bad = 0;
-    for (int64_t v = v_lo + gw; v < v_hi; v += nw) {
-        const int64_t b = d.rowptr[v], e = d.rowptr[v + 1];
-        const int64_t lo = d.base((int32_t)v), hi = d.id_end((int32_t)v);
-        const int32_t vl = (int32_t)(v - lo);  // v's id inside its graph, as its neighbours' rows hold it
-        for (int64_t k = b + lane; k < e; k += kWave) {
-            const int32_t ul = rows[k];
-            const int64_t u = (int64_t)ul + lo;
-            if (u < lo || u >= hi) continue;
-            if (u == v) bad |= kFullSelfLoop;
-            if (k + 1 < e && rows[k + 1] == ul) bad |= kFullDuplicate;
-            int64_t a = d.rowptr[u], z = d.rowptr[u + 1];
-            const int64_t end = z;
-            while (a < z) {  // first position of row u holding an id >= vl
-                const int64_t mid = (a + z) >> 1;
-                if (rows[mid] < vl) a = mid + 1;
-                else z = mid;
-            }
-            if (a == end || rows[a] != vl) bad |= kFullAsymmetric;
+    for (int64_t k0 = e_lo + gw * kWave; k0 < e_hi; k0 += nw * kWave) {
+        const int64_t k1 = min<int64_t>(k0 + kWave, e_hi) - 1, k = min(k0 + lane, k1);
+        int64_t v = row_owner(d, v_lo, v_hi, k0);
+        int64_t z = row_owner(d, v, min(v_hi, v + (k1 - k0) + 1 + 64 * kWave), k1);
+        if (d.rowptr[z + 1] <= k1) z = row_owner(d, z, v_hi, k1);  // a long run of empty rows in between
+        for (z += 1; z - v > 1;) {  // this lane's row
+            const int64_t mid = (v + z) >> 1;
+            if (d.rowptr[mid] <= k) v = mid;
+            else z = mid;
         }
+        if (k0 + lane > k1) continue;
+        const int64_t e = d.rowptr[v + 1], lo = d.base((int32_t)v), hi = d.id_end((int32_t)v);
+        const int32_t vl = (int32_t)(v - lo);  // v's id inside its graph, as its neighbours' rows hold it
+        const int32_t ul = rows[k];
+        const int64_t u = (int64_t)ul + lo;
+        if (u < lo || u >= hi) continue;
+        if (u == v) bad |= kFullSelfLoop;
+        if (k + 1 < e && rows[k + 1] == ul) bad |= kFullDuplicate;
+        int64_t a = d.rowptr[u], y = d.rowptr[u + 1];
+        const int64_t end = y;
+        while (a < y) {  // first position of row u holding an id >= vl
+            const int64_t mid = (a + y) >> 1;
+            if (rows[mid] < vl) a = mid + 1;
+            else y = mid;
+        }
+        if (a == end || rows[a] != vl) bad |= kFullAsymmetric;
     }
     for (int o = 32; o > 0; o >>= 1) bad |= __shfl_xor(bad, o);
     if (bad && lane == 0) atomicOr(flag, bad);
 }
 
-// A packed batch seen as one graph: union row starts (local offsets of graph
-// g shifted by its first entry), the first global id of each node's graph,
-// and each node's graph index.  A workgroup per graph at a time; also checks
-// each graph's row pointers (local rowptr[0] == 0, rowptr[n_g] == m_g,
-// non-decreasing) and flags bad_rows.  Graphs of at most small_n nodes and small_m entries (small_n < 0:
-// none) are colored elsewhere: their nodes get a negative graph index.
+// A packed batch seen as one graph: union row starts (local offsets of graph g shifted by its first entry), the
+// first global id of each node's graph, and each node's graph index.  A thread per node, its graph found by a
+// search of the node offsets (a workgroup per graph left the largest graph to one: 2.1 ms at 10^6 nodes); also
+// checks each graph's row pointers (local rowptr[0] == 0, rowptr[n_g] == m_g, non-decreasing) and flags bad_rows.
+// Graphs of at most small_n nodes and small_m entries (small_n < 0: none) are colored elsewhere: their nodes
+// get a negative graph index.
 static __global__ __launch_bounds__(kPrepBlock) void k_batch_union(const int64_t *node_off, const int64_t *edge_off,
                                                             const int32_t *rowptr_packed, int64_t graphs,
                                                             int64_t small_n, int64_t small_m,
                                                             int64_t *growptr, int32_t *gbase, int32_t *gidx,
                                                             Counters *ct) {
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
     int bad = 0;
-    for (int64_t g = blockIdx.x; g < graphs; g += gridDim.x) {
-        const int64_t n0 = node_off[g], ng = node_off[g + 1] - n0;
-        const int64_t e0 = edge_off[g], mg = edge_off[g + 1] - e0;
-        const int32_t *rp = rowptr_packed + n0 + g;  // graph g's n_g + 1 local row pointers
-        for (int64_t lv = threadIdx.x; lv <= ng; lv += blockDim.x) {
-            const int64_t a = rp[lv];
-            if (lv == 0) bad |= a != 0;
-            if (lv == ng) bad |= a != mg;
-            if (lv < ng) {
-                const int64_t e = rp[lv + 1];
-                bad |= e < a || a < 0 || e > mg;
-                growptr[n0 + lv] = e0 + a;
-                gbase[n0 + lv] = (int32_t)n0;
-                gidx[n0 + lv] = ng <= small_n && mg <= small_m ? -1 : (int32_t)g;
-            }
-        }
+    for (int64_t g = gt; g < graphs; g += nt) {  // the ends of every graph, empty ones too
+        const int32_t *rp = rowptr_packed + node_off[g] + g;
+        bad |= rp[0] != 0 || rp[node_off[g + 1] - node_off[g]] != edge_off[g + 1] - edge_off[g];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) growptr[node_off[graphs]] = edge_off[graphs];
+    const int64_t n = node_off[graphs];
+    for (int64_t v = gt; v < n; v += nt) {
+        int64_t g = 0, z = graphs;  // the last graph with node_off[g] <= v (empty graphs share the next one's offset)
+        while (z - g > 1) {
+            const int64_t mid = (g + z) >> 1;
+            if (node_off[mid] <= v) g = mid;
+            else z = mid;
+        }
+        const int64_t n0 = node_off[g], ng = node_off[g + 1] - n0, e0 = edge_off[g], mg = edge_off[g + 1] - e0;
+        const int64_t a = rowptr_packed[v + g], e = rowptr_packed[v + g + 1];
+        bad |= e < a || a < 0 || e > mg;
+        growptr[v] = e0 + a;
+        gbase[v] = (int32_t)n0;
+        gidx[v] = ng <= small_n && mg <= small_m ? -1 : (int32_t)g;
+    }
+    if (gt == 0) growptr[n] = edge_off[graphs];
     if (__ballot(bad) && lane_id() == 0) ct->bad_rows = 1;
 }
 
@@ -2207,10 +2232,10 @@ __device__ __forceinline__ void conflict_step(const D &d, const RoundIn &in, con
     if (T > 1) conflict_wide_teams(d, in, os, r, un, G, T, discard, seg_base, s_cnt, s_deg);
     // Without teams: a wavefront per node, or, when W nodes are many (at least four per
     // wavefront), a quarter wavefront per W node so that four latency chains overlap.
-    const bool quarter = T == 1 && (int64_t)nW >= 4 * nw;
+    const bool quarter = T == 1 && (int64_t)nW >= 2 * nw;
     for (int ph = 0; ph < 2 && T == 1; ++ph) {
         const int64_t cnt = ph == 0 && quarter ? nW : nWM - nW;  // nodes of this phase's class(es)
-        const int S = ph == 0 && !quarter ? kWave : cnt >= 8 * nw ? 8 : cnt >= 4 * nw ? 16 : kWave;
+        const int S = ph == 0 && !quarter ? kWave : cnt >= 32 * nw ? 4 : cnt >= 8 * nw ? 8 : cnt >= 2 * nw ? 16 : kWave;
         const int64_t lo = ph == 0 ? 0 : (quarter ? nW : nWM), hi = ph == 0 && quarter ? nW : nWM;
         const int per = kWave / S, gl = lane % S;
         if constexpr (kSplitDev<D>) {

@@ -115,6 +115,7 @@ struct DBuf {
 struct Params {
     int light_max = kDefaultLightMax;
     int hub_min = kDefaultHubMin;
+    bool hub_auto = true;   // no hub_min_degree given: chosen by the graph's size
     bool check_ids = true;
     bool full = false;      // IPGC_VALIDATE_FULL: also a simple symmetric graph
     bool stepped = false;

@@ -591,7 +591,8 @@ int Server::admit_staged() {
         if (P.full) {
             // sorted rows in the job's ring slots (the rings are built over them next), then the checks
             k_full_sort<<<(int)std::min<int64_t>(j.n, 65536), kSortBlock, 0, s>>>(d, v0, v0 + j.n, lower.p, gerr.p + slot);
-            k_full_check<<<std::max(1, pblocks), kPrepBlock, 0, s>>>(d, v0, v0 + j.n, lower.p, gerr.p + slot,
+            const int cblocks = (int)std::max<int64_t>(1, std::min<int64_t>(16384, (j.m + kPrepBlock - 1) / kPrepBlock));
+            k_full_check<<<cblocks, kPrepBlock, 0, s>>>(d, v0, v0 + j.n, lower.p, gerr.p + slot,
                                                                     gerr.p + slot);
         }
         k_srv_prep<<<std::max(1, pblocks), 256, 0, s>>>(d, (int32_t)v0, j.n, slot, gerr.p);
