@@ -27,15 +27,29 @@ struct SmallLists {
     uint16_t wl[2][kSmallNodes];    // worklists: short rows from the front, long rows from the back
 };
 
+// Sparse graphs (no row longer than kRowsDegree) leave the worklist for the row rounds instead of the core: the
+// uncolored nodes' rows among themselves in shared memory, by rank.  A bit matrix of a sparse graph is mostly
+// zeros: reading its rows took 8 us a round for 1000 nodes of degree 8, reading the lists takes 1 us.
+constexpr int kRowsNodes = 4096;     // four a thread
+constexpr int kRowsEntries = 40960;  // sum of the nodes' degrees
+constexpr int kRowsDegree = 63;      // so that 64 color bits always have a free one
+
+struct SmallRows {
+    uint16_t adj[kRowsEntries];  // ranks of each node's uncolored neighbours, ascending if the rows are
+    int16_t s[kRowsNodes];       // > 0 committed in these rounds, -t tentative
+    int left[2];                 // uncolored nodes after each round, by parity
+};
+
 struct SmallShared {
     union {
         SmallLists a;
         CoreShared core;
+        SmallRows rows;
     };
     uint64_t bits[kSmallNodes / 64];  // uncolored nodes, when the core starts
     int32_t pre[kSmallNodes / 64];    // and the number of them before each word
     int nl[2], nw[2];                 // entries of each worklist, short and long rows
-    int bad, descents, starts;
+    int bad, descents, starts, maxdeg;
     unsigned long long deg;
 };
 static_assert(sizeof(SmallShared) <= 160 * 1024 - 1024, "one workgroup's shared memory");
@@ -93,9 +107,10 @@ __device__ __forceinline__ int wave_append(bool flag, int *count) {
     return at + __popcll(m & lanes_below());
 }
 
+// gone: degrees of the nodes this thread commits.
 // One round's conflict tests, commits and pushes of the short rows, a lane each, two in flight per lane.
 __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, const int32_t *ci, int32_t m, int32_t *out,
-                                            int p, bool sorted, bool deg) {
+                                            int p, bool sorted, int &gone) {
     constexpr int K = 2, C = 4;
     const int nl = sh.nl[p];
     const uint16_t *cur = sh.a.wl[p];
@@ -145,7 +160,7 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
             if (v[j] < 0 || l) continue;
             sh.a.c[v[j]] = (int16_t)t[j];
             out[v[j]] = t[j];
-            if (deg) atomicAdd(&sh.deg, 0ull - (unsigned long long)(e[j] - b[j]));
+            gone += e[j] - b[j];
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -165,7 +180,7 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
 // The same for the long rows, by groups of S lanes (16, so that four rows overlap in a wavefront, or a
 // wavefront when there are few of them).
 __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, const int32_t *ci, int32_t *out, int p,
-                                           bool sorted, bool deg) {
+                                           bool sorted, int &gone) {
     constexpr int C = 4;
     const int nw = sh.nw[p], S = nw >= kCore / kWave * 4 ? 16 : kWave, per = kCore / S;
     const int lane = lane_id(), gl = threadIdx.x % S;
@@ -200,7 +215,7 @@ __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, c
         if (gl == 0) {
             sh.a.c[v] = (int16_t)t;
             out[v] = t;
-            if (deg) atomicAdd(&sh.deg, 0ull - (unsigned long long)(e - b));
+            gone += e - b;
         }
         if (t > kMaskColors) continue;
         const unsigned long long bit = 1ull << (t - 1);
@@ -213,6 +228,139 @@ __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, c
                 if (u[q] >= 0) atomicOr((unsigned long long *)&sh.a.mask[u[q]], bit);
         }
     }
+}
+
+// Row rounds: from round r on, `nact` uncolored nodes; fresh: all nodes of the graph, before any round, else those of
+// worklist p.  Up to four nodes a thread, each with its rank, its row and the colors it may not take.  A round has
+// two steps: conflict (a smaller neighbour with the same color in |s|; winners turn their s positive at once, which
+// changes no test) and, for the losers, the colors that neighbours have committed, whose entries leave the row.
+__device__ __forceinline__ int32_t small_rows(SmallShared &sh, const SmallArgs &a, const int32_t *rp, const int32_t *ci,
+                                              int32_t m, int32_t *out, int p, int32_t r, int nact, bool fresh, bool sorted) {
+    constexpr int K = kRowsNodes / kCore;
+    const int tid = threadIdx.x, lane = lane_id();
+    const bool keep = a.trace != nullptr;
+    int64_t degsum = (int64_t)sh.deg;
+    int v[K], b[K], len[K], rank[K], at[K], t[K];
+    uint64_t mask[K];
+    if (!fresh) {
+        for (int k = tid; k < kSmallNodes / 64; k += kCore) sh.bits[k] = 0;
+        __syncthreads();
+    }
+    int sum = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        const int i = j * kCore + tid;
+        v[j] = i >= nact ? -1 : fresh ? i : (int)sh.a.wl[p][i];
+        mask[j] = v[j] >= 0 && !fresh ? sh.a.mask[v[j]] : 0ull;
+        const Bounds<int32_t> row = v[j] >= 0 ? row_of(rp, v[j]) : Bounds<int32_t>{0, 0};
+        b[j] = row.b;
+        len[j] = row.e - row.b;
+        sum += len[j];
+        t[j] = __ffsll((unsigned long long)~mask[j]);
+        if (v[j] >= 0 && !fresh) atomicOr((unsigned long long *)&sh.bits[v[j] >> 6], 1ull << (v[j] & 63));
+    }
+    __syncthreads();
+    int total;
+    if (!fresh) {
+        const int pc = tid < kSmallNodes / 64 ? __popcll(sh.bits[tid]) : 0;
+        const int ex = block_scan(pc, &total);
+        if (tid < kSmallNodes / 64) sh.pre[tid] = ex;
+    }
+    int first = block_scan(sum, &total);  // (its barriers: the worklist's state has been read)
+    __syncthreads();
+    const auto rank_of = [&](int32_t u) {
+        if (fresh) return u;
+        const uint64_t word = sh.bits[u >> 6], bit = 1ull << (u & 63);
+        return word & bit ? sh.pre[u >> 6] + (int)__popcll(word & (bit - 1)) : -1;
+    };
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        at[j] = first;
+        first += len[j];
+        rank[j] = v[j] >= 0 ? rank_of(v[j]) : 0;
+        int w = 0;
+        for (int q0 = 0; q0 < len[j]; q0 += 4) {
+            int32_t u[4];
+            load4(ci, b[j] + q0, m, -1, u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q0 + q >= len[j]) continue;
+                const int x = rank_of(u[q]);
+                if (x >= 0 && x != rank[j]) sh.rows.adj[at[j] + w++] = (uint16_t)x;
+            }
+        }
+        if (keep && v[j] >= 0) b[j] = len[j];  // the degree, for the record
+        len[j] = w;
+        if (v[j] >= 0) sh.rows.s[rank[j]] = (int16_t)-t[j];
+    }
+    if (tid == 0) sh.rows.left[r & 1] = 0;
+    core_sync();
+    uint32_t act = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) act |= (v[j] >= 0 ? 1u : 0u) << j;
+    for (; nact > 0; ++r) {
+        if (keep && tid == 0 && r - 1 < a.trace_cap) {
+            a.trace[r - 1] = nact;
+            a.trace_deg[r - 1] = degsum;
+        }
+        if (tid == 0) sh.rows.left[(r + 1) & 1] = 0;  // last read before the barrier that ended the round before
+        uint32_t won = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (!(act >> j & 1u)) continue;
+            bool lose = false;
+            for (int q0 = 0; q0 < len[j] && !lose; q0 += 4) {
+                int x[4], c[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = q0 + q < len[j] ? (int)sh.rows.adj[at[j] + q0 + q] : kRowsNodes;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[q] = x[q] < rank[j] ? abs((int)sh.rows.s[x[q]]) : 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) lose |= c[q] == t[j];
+                if (sorted && x[3] > rank[j]) break;
+            }
+            if (lose) continue;
+            won |= 1u << j;
+            sh.rows.s[rank[j]] = (int16_t)t[j];
+            out[v[j]] = t[j];
+        }
+        act &= ~won;
+        int some = __popc(act);
+        for (int o = 32; o > 0; o >>= 1) some += __shfl_xor(some, o);
+        if (lane == 0 && some) atomicAdd(&sh.rows.left[r & 1], some);
+        if (keep) {
+            int gone = 0;
+#pragma unroll
+            for (int j = 0; j < K; ++j) gone += won >> j & 1u ? b[j] : 0;
+            gone = (int)wave_sum(gone);
+            if (lane == 0 && gone) atomicAdd(&sh.deg, 0ull - (unsigned long long)gone);
+        }
+        core_sync();
+        nact = sh.rows.left[r & 1];
+        degsum = (int64_t)sh.deg;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (!(act >> j & 1u)) continue;
+            int w = 0;
+            for (int q0 = 0; q0 < len[j]; q0 += 4) {
+                int x[4], c[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = q0 + q < len[j] ? (int)sh.rows.adj[at[j] + q0 + q] : -1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[q] = x[q] >= 0 ? (int)sh.rows.s[x[q]] : 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (c[q] > 0 && c[q] <= kMaskColors) mask[j] |= 1ull << (c[q] - 1);
+                    if (c[q] < 0) sh.rows.adj[at[j] + w++] = (uint16_t)x[q];
+                }
+            }
+            len[j] = w;
+            t[j] = __ffsll((unsigned long long)~mask[j]);
+            sh.rows.s[rank[j]] = (int16_t)-t[j];
+        }
+        core_sync();
+    }
+    return r - 1;
 }
 
 static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
@@ -228,15 +376,16 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
     // Checks: the CSR's ends, row pointers non-decreasing inside [0, m], ids inside [0, n); and whether every
     // row is sorted: the entries not above their predecessor are then all first entries of rows.
     if (tid == 0) {
-        sh.bad = sh.descents = sh.starts = 0;
+        sh.bad = sh.descents = sh.starts = sh.maxdeg = 0;
         sh.nl[0] = sh.nw[0] = 0;
     }
     __syncthreads();
-    int bad = 0, starts = 0, descents = 0;
+    int bad = 0, starts = 0, descents = 0, maxdeg = 0;
     for (int v = tid; v < n; v += kCore) {
         const int64_t b = rp[v], e = rp[v + 1];
         if (b < 0 || e < b || e > m) bad |= 1;
         else if (b > 0 && b < e) starts += ci[b] <= ci[b - 1];
+        maxdeg = max(maxdeg, (int)min<int64_t>(e - b, INT32_MAX));
     }
     if (tid == 0) {
         if (rp[0] != 0 || rp[n] != m) bad |= 4;
@@ -267,6 +416,8 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
     descents = (int)wave_sum(descents);
     if (lane == 0 && starts) atomicAdd(&sh.starts, starts);
     if (lane == 0 && descents) atomicAdd(&sh.descents, descents);
+    for (int o = 32; o > 0; o >>= 1) maxdeg = max(maxdeg, __shfl_xor(maxdeg, o));
+    if (lane == 0) atomicMax(&sh.maxdeg, maxdeg);
     __syncthreads();
     bad = sh.bad;
     const bool sorted = sh.starts == sh.descents;
@@ -288,7 +439,11 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
     int64_t deg = m;
     const bool keep = a.trace != nullptr;
     CoreState s;
-    if (n > kCore) {
+    const bool sparse = sh.maxdeg <= kRowsDegree;
+    bool rows = sparse && n <= kRowsNodes && m <= kRowsEntries;
+    if (rows) {
+        sh.deg = (unsigned long long)m;
+    } else if (n > kCore) {
         for (int v0 = 0; v0 < n; v0 += kCore) {
             const int v = v0 + tid;
             const bool has = v < n, wide = has && rp[v + 1] - rp[v] > kSmallLight;
@@ -317,15 +472,33 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
             }
             if (tid == 0) sh.nl[p ^ 1] = sh.nw[p ^ 1] = 0;
             core_sync();
-            small_wide(sh, rp, ci, out, p, sorted, keep);
-            small_light(sh, rp, ci, (int32_t)m, out, p, sorted, keep);
+            int gone = 0;
+            small_wide(sh, rp, ci, out, p, sorted, gone);
+            small_light(sh, rp, ci, (int32_t)m, out, p, sorted, gone);
+            gone = (int)wave_sum(gone);
+            if (lane == 0 && gone) atomicAdd(&sh.deg, 0ull - (unsigned long long)gone);
             core_sync();
             p ^= 1;
             ++r;
             nact = sh.nl[p] + sh.nw[p];
             core_sync();  // the counts are cleared in the next round, the degree sum read
+            rows = sparse && nact <= kRowsNodes && sh.deg <= kRowsEntries;
+            if (rows) break;
         }
         deg = (int64_t)sh.deg;
+    }
+    if (rows) {
+        const int32_t last = small_rows(sh, a, rp, ci, (int32_t)m, out, p, r, nact, n <= kRowsNodes && r == 1, sorted);
+        if (tid == 0) {
+            if (a.grounds) a.grounds[g] = last;
+            if (!a.node_off) {
+                a.ct->rounds = last;
+                a.ct->finished = 1;
+            }
+        }
+        return;
+    }
+    if (n > kCore) {
         // hand over to the core: ranks from a bit per uncolored node, the nodes' state through shared memory
         for (int k = tid; k < kSmallNodes / 64; k += kCore) sh.bits[k] = 0;
         __syncthreads();

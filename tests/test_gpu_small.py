@@ -64,6 +64,19 @@ def test_small_graphs_with_unsorted_rows(g):
     check(g, rp, ci, validate=1)
 
 
+# Row rounds: at and past their nodes (4096), entries (40 960: 10 cliques of 64 have 40 320) and row length (63), from
+# the first round and after list rounds.
+ROWS = [cliques(10, 64), cliques(11, 64), cliques(9, 65), cliques(60, 64), gg.path(4096), gg.path(4097), gg.cycle(4095),
+        gg.erdos_renyi(4096, 4.0, gg.key(85, 0)), gg.erdos_renyi(4097, 4.0, gg.key(85, 1)), gg.erdos_renyi(9000, 20.0, gg.key(85, 2)),
+        gg.star(64, 0), gg.star(63, 63), gg.star(62, 30), gg.crown(64), gg.complete(64), gg.complete(65)]
+
+
+@pytest.mark.parametrize("g", ROWS, ids=lambda g: "%s_%d" % (g.name, g.n))
+def test_row_rounds(g):
+    check(g)
+    check(g, *gg.shuffle_rows(g, 7), noalloc=True)
+
+
 def test_small_graphs_with_self_loops_and_repeated_entries():
     g = gg.rmat(12, 8, gg.key(82, 0))
     deg = g.degrees()
