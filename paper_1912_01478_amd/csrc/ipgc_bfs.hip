@@ -98,9 +98,13 @@ __device__ __forceinline__ int32_t frontier_at(const BfsDev &d, int p, const int
 // Row entries k0, k0 + step, ... (P of them) below e: claims their unvisited nodes for level `next`.  The
 // P loads of each kind are in flight together.  A first look at dist reads through the caches: a value
 // other than -1 is final, a stale -1 only leads to the second look, which does not (most entries of a
-// large level lead to nodes reached long before, and those are settled in the caches).  Winners go to
-// this workgroup's segment, or to the overflow list.
-template <int P>
+// large level lead to nodes reached long before, and those are settled in the caches).  Without the second
+// look (Twice) a stale -1 costs a failed claim instead of a trip to memory for all: the rows that one thread
+// walks, whose level lasts as long as its longest chain of trips (sparse random graph of 100 003 nodes,
+// with 16 entries in flight instead of 4: 347 -> 307 us a search with one look, 354 with two).
+// Winners go to this workgroup's segment, or to the overflow list, whose places the lanes of a wavefront
+// take together (80 ns for every atomic on one address).
+template <int P, bool Twice = true>
 __device__ __forceinline__ void visit(const BfsDev &d, int64_t k0, int32_t step, int64_t e, int32_t next, int dst,
                                       int *s_cnt) {
     int32_t u[P];
@@ -110,15 +114,25 @@ __device__ __forceinline__ void visit(const BfsDev &d, int64_t k0, int32_t step,
 #pragma unroll
     for (int j = 0; j < P; ++j)
         open[j] = u[j] >= 0 && __hip_atomic_load(&d.dist[u[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == -1;
+    if (Twice) {
 #pragma unroll
-    for (int j = 0; j < P; ++j)
-        if (open[j]) open[j] = __hip_atomic_load(&d.dist[u[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == -1;
+        for (int j = 0; j < P; ++j)
+            if (open[j]) open[j] = __hip_atomic_load(&d.dist[u[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == -1;
+    }
+#pragma unroll
+    for (int j = 0; j < P; ++j) open[j] = open[j] && atomicCAS(&d.dist[u[j]], -1, next) == -1;
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-        if (!open[j] || atomicCAS(&d.dist[u[j]], -1, next) != -1) continue;
+        if (!open[j]) continue;
         const int p = atomicAdd(s_cnt, 1);
-        if (p < d.cap) d.seg[dst][(int64_t)blockIdx.x * d.cap + p] = u[j];
-        else d.ovf[dst][atomicAdd(&d.ctl->ovf_cnt[next % 3], 1)] = u[j];
+        if (p < d.cap) {
+            d.seg[dst][(int64_t)blockIdx.x * d.cap + p] = u[j];
+        } else {
+            const uint64_t full = __ballot(1);  // the lanes that are here
+            int at = 0;
+            if ((full & lanes_below()) == 0) at = atomicAdd(&d.ctl->ovf_cnt[next % 3], (int)__popcll(full));
+            d.ovf[dst][__builtin_amdgcn_readfirstlane(at) + __popcll(full & lanes_below())] = u[j];
+        }
     }
 }
 
@@ -190,8 +204,11 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
         __syncthreads();
         // No barrier here: this level fills the lists and counts of parity dst, last read in level
         // lvl - 1, which every workgroup has left.
-        for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < items; i0 += nt) {
-            const int64_t i = i0 + threadIdx.x;
+        // A wavefront's 64 items are next to each other, a workgroup's wavefronts far apart: nodes reached from one
+        // row, and the low ids of an R-MAT graph, are wide together, and 1024 neighbours in the list left one
+        // workgroup with a million entries (R-MAT of 2^20 nodes: 1.88 -> 0.60 ms a search; 100 003 nodes: 282 -> 235 us).
+        for (int64_t i0 = (int64_t)blockIdx.x * kWave; i0 < items; i0 += nt) {
+            const int64_t i = i0 + (int64_t)w * gridDim.x * kWave + lane;
             int32_t v = -1;
             if (i < items) {
                 if (topo) v = d.dist[i] == lvl ? (int32_t)i : -1;
@@ -202,7 +219,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
                 if (e - b > kHubDeg) d.hub[atomicAdd(&d.ctl->hubs[lvl % 3], 1)] = v;
                 else if (e - b > kLightDeg) heavy[atomicAdd(&s_heavy, 1)] = v;  // at most a workgroup's threads
                 else
-                    for (int64_t k = b; k < e; k += 4) visit<4>(d, k, 1, e, next, dst, &s_cnt);
+                    for (int64_t k = b; k < e; k += 16) visit<16, false>(d, k, 1, e, next, dst, &s_cnt);
             }
             __syncthreads();
             const int nh = s_heavy;
@@ -319,7 +336,10 @@ int bfs_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m,
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(k_bfs), kBlock, 0));
     // the frontier view keeps one prefix entry per workgroup plus the overflow list in a block of kBlock threads
     const int cap_grid = std::max(1, std::min(std::min(kMaxRoundBlocks, kBlock) - 1, cus * std::max(1, per_cu)));
-    const int64_t want = P.workgroups > 0 ? P.workgroups : (n + 4 * kBlock - 1) / (4 * kBlock);
+    // Two nodes or 16 entries a thread: more workgroups make the barriers dearer, fewer walk more rows one after the
+    // other (sparse random graph of 100 003 nodes, with 25 / 50 / 100 / 200 workgroups: 260 / 233 / 235 / 245 us a search;
+    // R-MAT graph of 65 536 nodes and 1.8 million entries, with 32 / 64 / 128: 304 / 248 / 231 us).
+    const int64_t want = P.workgroups > 0 ? P.workgroups : std::max(n / (2 * kBlock), m / (16 * kBlock)) + 1;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(want, cap_grid));
 
     int64_t H;

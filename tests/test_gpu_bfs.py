@@ -94,6 +94,22 @@ def test_bfs_rows_spread_over_the_grid(g):
             check(g, source, mode, workgroups=3)
 
 
+def two_levels(mids, leaves):
+    """A source next to `mids` nodes, each next to `leaves` nodes of its own."""
+    src = np.concatenate([np.zeros(mids, dtype=np.int64), np.repeat(np.arange(1, mids + 1), leaves)])
+    return gg.from_pairs(1 + mids + mids * leaves, src, np.arange(1, 1 + mids + mids * leaves), "%dx%d" % (mids, leaves))
+
+
+# One wavefront's frontier nodes reach more nodes than the workgroup's segment holds (n / 64 + 1024): thread rows
+# at the edges of 16 entries and of the 32 of a thread, wavefront rows, and several levels on two workgroups.
+@pytest.mark.parametrize("g", [two_levels(64, 31), two_levels(64, 30), two_levels(63, 32), two_levels(33, 2047), two_levels(64, 17),
+                               two_levels(64, 16), two_levels(64, 15)], ids=lambda g: g.name)
+def test_bfs_overflow_from_one_wavefront(g):
+    for mode in MODES:
+        check(g, 0, mode, workgroups=64)
+        check(g, g.n - 1, mode)
+
+
 def test_bfs_checks_come_before_any_row_is_read():
     """Bad row pointers and ids anywhere in the entry array, also in entries past the last full stride."""
     import paper_1912_01478_amd as ip
