@@ -15,7 +15,8 @@
 // no global atomic); a segment that fills up spills into an overflow list
 // through one atomicAdd per spilled node.  All levels run in one cooperative
 // launch with the grid barrier of the coloring kernels, one barrier per level
-// and one more in levels with hubs.
+// and one more in levels with hubs.  Small graphs run on one workgroup
+// (k_bfs_one), with the same distances and levels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,6 +39,13 @@ constexpr int kHeavyPerBlock = 1024;
 // about 12 us, what the extra barrier and the staging of the hub step cost; the widest row of an
 // R-MAT graph of 2^22 nodes (160 000 entries) kept one for 4 ms.
 constexpr int kHubDeg = 2048;
+// Graphs of at most so many nodes and entries are searched by one workgroup: a level takes 4 us there and 14 us
+// over the grid, but one compute unit reads 256 entries a microsecond.  One workgroup / the grid, a search:
+// 1000 nodes and 8 000 entries 52 / 129 us, 20 000 and 80 000 129 / 205 us, R-MAT 8192 and 204 000 151 / 169 us,
+// R-MAT 16 384 and 228 000 190 / 186 us, 32 000 and 256 000 246 / 218 us.
+constexpr int kOneNodes = 32768;
+constexpr int64_t kOneEntries = 3 << 16;
+constexpr int kOneHubDeg = 1024;  // there, rows longer than this are walked by all threads together
 constexpr int kHubChunk = 4 * kWave;  // hub entries per wavefront step
 
 // Control block of one call: cleared before it, read back after it.
@@ -245,6 +253,86 @@ __global__ __launch_bounds__(kBlock) void k_bfs(BfsDev d) {
     }
 }
 
+// The whole search on one workgroup: frontiers and reached nodes in shared memory, so that a level is two trips to
+// memory (row bounds, entries) and workgroup barriers.
+struct OneShared {
+    uint16_t list[2][kOneNodes];
+    uint32_t seen[kOneNodes / 32];
+    uint16_t wide[kBlock];  // of the frontier nodes at hand: wavefront rows from the front, rows for all from the back
+    int cnt[2];
+    int rows, hubs;
+};
+
+// visit() for one workgroup
+template <int P>
+__device__ __forceinline__ void visit_one(const BfsDev &d, OneShared &sh, int32_t k0, int32_t step, int32_t e, int32_t next,
+                                          int dst) {
+    int32_t u[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) u[j] = (int64_t)k0 + (int64_t)j * step < e ? d.colidx[k0 + j * step] : -1;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        if (u[j] < 0) continue;
+        const uint32_t bit = 1u << (u[j] & 31);
+        if ((sh.seen[u[j] >> 5] & bit) || (atomicOr(&sh.seen[u[j] >> 5], bit) & bit)) continue;
+        sh.list[dst][atomicAdd(&sh.cnt[dst], 1)] = (uint16_t)u[j];
+        d.dist[u[j]] = next;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_bfs_one(BfsDev d) {
+    __shared__ OneShared sh;
+    if (d.ctl->bad | d.ctl->bad_ends) return;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    for (int k = tid; k < kOneNodes / 32; k += kBlock) sh.seen[k] = 0;
+    __syncthreads();
+    if (tid == 0) {
+        sh.list[0][0] = (uint16_t)d.source;
+        sh.seen[d.source >> 5] = 1u << (d.source & 31);
+        sh.cnt[0] = 1;
+    }
+    __syncthreads();
+    for (int32_t lvl = 0;; ++lvl) {
+        const int src = lvl & 1, dst = src ^ 1, size = sh.cnt[src];
+        if (tid == 0) {
+            if (lvl < d.trace_cap) d.trace[lvl] = size;
+            if (size == 0) {
+                d.ctl->levels = lvl;
+                d.ctl->done = 1;
+            }
+            sh.cnt[dst] = sh.rows = sh.hubs = 0;
+        }
+        if (size == 0) return;
+        __syncthreads();
+        for (int i0 = 0; i0 < size; i0 += kBlock) {
+            const int i = i0 + tid;
+            if (i < size) {
+                const int32_t v = sh.list[src][i];
+                const int32_t b = d.rowptr[v], e = d.rowptr[v + 1];
+                if (e - b > kOneHubDeg) sh.wide[kBlock - 1 - atomicAdd(&sh.hubs, 1)] = (uint16_t)v;
+                else if (e - b > kLightDeg) sh.wide[atomicAdd(&sh.rows, 1)] = (uint16_t)v;
+                else
+                    for (int32_t k = b; k < e; k += 16) visit_one<16>(d, sh, k, 1, e, lvl + 1, dst);
+            }
+            __syncthreads();
+            const int rows = sh.rows, hubs = sh.hubs;
+            for (int h = w; h < rows; h += kBlock / kWave) {
+                const int32_t v = sh.wide[h];
+                const int32_t b = d.rowptr[v], e = d.rowptr[v + 1];
+                for (int64_t k = b + lane; k < e; k += 8 * kWave) visit_one<8>(d, sh, (int32_t)k, kWave, e, lvl + 1, dst);
+            }
+            for (int h = 0; h < hubs; ++h) {
+                const int32_t v = sh.wide[kBlock - 1 - h];
+                const int32_t b = d.rowptr[v], e = d.rowptr[v + 1];
+                for (int64_t k = b + tid; k < e; k += 4 * kBlock) visit_one<4>(d, sh, (int32_t)k, kBlock, e, lvl + 1, dst);
+            }
+            __syncthreads();
+            if (tid == 0) sh.rows = sh.hubs = 0;
+            __syncthreads();
+        }
+    }
+}
+
 // Buffers of one device, kept between calls (they only grow).
 struct BfsWorkspace {
     DBuf<int32_t> seg0, seg1, cnt0, cnt1, ovf0, ovf1, hub, tr;
@@ -385,13 +473,20 @@ int bfs_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m,
     d.bar = w.bar.p;
     TRY(barrier_limit_ticks(dev, P.barrier_ms, &d.bar_limit));
     TRY(clear(w.ctl.p, sizeof(BfsCtl), s));
-    TRY(clear(w.bar.p, sizeof(Barrier), s));
+    // sweeps over every node are what TOPOLOGY asks for, and a wait limit of -1 gives up at the first barrier
+    const bool one = n <= kOneNodes && m <= kOneEntries && P.workgroups == 0 && P.mode != IPGC_MODE_TOPOLOGY && P.barrier_ms >= 0;
+    if (!one) TRY(clear(w.bar.p, sizeof(Barrier), s));
     // the search reads no row when the checks fail, so the host waits once, at the end
     const int64_t work = n + (P.check_ids ? m / 8 : 0);
     k_bfs_prep<<<(int)std::min<int64_t>(4096, (work + 255) / 256), 256, 0, s>>>(d, P.check_ids ? 1 : 0);
     HIP_TRY(hipGetLastError());
-    void *args[] = {&d};
-    HIP_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_bfs), dim3(grid), dim3(kBlock), args, 0, s));
+    if (one) {
+        k_bfs_one<<<1, kBlock, 0, s>>>(d);
+        HIP_TRY(hipGetLastError());
+    } else {
+        void *args[] = {&d};
+        HIP_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_bfs), dim3(grid), dim3(kBlock), args, 0, s));
+    }
     HIP_TRY(hipMemcpyAsync(w.host_ctl, w.ctl.p, sizeof(BfsCtl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     const BfsCtl h = *w.host_ctl;

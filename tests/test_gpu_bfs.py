@@ -110,6 +110,19 @@ def test_bfs_overflow_from_one_wavefront(g):
         check(g, g.n - 1, mode)
 
 
+# One workgroup: at and past its nodes (32 768) and entries (196 608), rows at the edges of a thread's (32), a
+# wavefront's (1024) and those for all threads, frontiers of more than 1024 nodes, many levels, unreached nodes.
+@pytest.mark.parametrize("g", [gg.empty(1), gg.path(2), gg.path(3000), gg.star(32767, 0), gg.star(32767, 32767), gg.star(32768, 32768),
+                               gg.path(32768), gg.complete_bipartite(96, 1024), gg.complete_bipartite(95, 1025), gg.complete(443),
+                               gg.complete(444), two_levels(1000, 32), two_levels(990, 33), two_levels(31, 1024), two_levels(31, 1023),
+                               gg.erdos_renyi(32768, 3.0, gg.key(912, 0)), gg.erdos_renyi(32769, 3.0, gg.key(912, 1)),
+                               gg.rmat(13, 12, gg.key(912, 2)), gg.rmat(15, 3, gg.key(912, 3))], ids=lambda g: "%s_%d" % (g.name, g.n))
+def test_bfs_on_one_workgroup(g):
+    for source in sorted({0, g.n // 2, g.n - 1}):
+        check(g, source, "hybrid")
+        check(g, source, "data")
+
+
 def test_bfs_checks_come_before_any_row_is_read():
     """Bad row pointers and ids anywhere in the entry array, also in entries past the last full stride."""
     import paper_1912_01478_amd as ip
