@@ -572,6 +572,11 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
     if (n_wide > 0) TRY(clear(ws.F.p, (size_t)(m + n + 64), s));
     if (P.light == 0 || (P.light < 0 && n_wide > 0)) d.light_pull = kPushAll;
     else d.light_pull = n_wide > 0 ? kPullLight : kPullOnly;
+    // Graphs of (almost) class L alone: most neighbours of a round's winners are committed, and their tags (a byte a
+    // node) stay in the L2s where their masks (8 bytes) do not: 1 000 003 nodes of degree 16 1.24 -> 1.07 ms.  Where
+    // wide nodes are many, the neighbours are mostly those, uncommitted, their masks hot: R-MAT of 2^22 nodes 20.2 -> 21.7
+    // ms, 160 graphs of both kinds 52.8 -> 55.3.
+    d.push_by_tag = n_wide <= n / 64 && !P.racy && !d.gidx;
     d.racy = P.racy ? 1 : 0;
     d.tail_groups = P.tail_groups;
     d.discard = P.mode == IPGC_MODE_REBUILD ? 1 : 0;

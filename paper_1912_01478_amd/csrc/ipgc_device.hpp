@@ -222,6 +222,7 @@ struct DevT {
     int32_t racy;            // in-place mode: losers uncolor at once, L assigns avoid in-flight tentatives
     int32_t parts;           // a union of many graphs, and a multiple of 8 workgroups: its parts stay on one XCD each
     int32_t discard;         // topology-driven rounds keep no worklist; it is rebuilt when data rounds start
+    int32_t push_by_tag;     // class L pushes into the masks of uncommitted neighbours, without a look at them
     int32_t core_max;        // worklists of at most this many nodes are left to k_core_rounds (0: none)
     int32_t tail_groups;     // workgroups that stay in the round loop for small data-driven rounds (0: all)
     uint64_t bar_limit;      // wall-clock ticks a grid-barrier wait may last
@@ -1803,8 +1804,9 @@ __device__ __forceinline__ void light_conflict(const D &d, const ClassView &cv, 
         un.u[kUCommits] += __popc(win);
         un.u[kUConflictNodes] += __popc(act);
         un.u[kUConflictEntries] += read;
-        // push modes: bit t - 1 into every neighbour's color mask (t <= d + 1 <= 33), read first,
-        // the atomic only where the bit is missing
+        // push modes: bit t - 1 into every neighbour's color mask (t <= d + 1 <= 33); the mask is read first and
+        // the atomic done only where the bit is missing, or (push_by_tag) the neighbour's tag is and the
+        // atomic done only where the neighbour is uncommitted
         if (!pull_only && win) {
             for (int32_t q0 = 0;; q0 += C) {
                 int32_t w[K][C];
@@ -1816,10 +1818,17 @@ __device__ __forceinline__ void light_conflict(const D &d, const ClassView &cv, 
                     for (int q = 0; q < C; ++q) w[j][q] = a && q0 + q < len[j] ? w[j][q] + gb[j] : -1;
                 }
                 uint64_t mw[K][C];
+                if (d.push_by_tag) {
     #pragma unroll
-                for (int j = 0; j < K; ++j)
+                    for (int j = 0; j < K; ++j)
     #pragma unroll
-                    for (int q = 0; q < C; ++q) mw[j][q] = w[j][q] >= 0 ? d.mask[w[j][q]] : ~0ull;
+                        for (int q = 0; q < C; ++q) mw[j][q] = w[j][q] >= 0 && !(d.tag[w[j][q]] & kDone) ? 0ull : ~0ull;
+                } else {
+    #pragma unroll
+                    for (int j = 0; j < K; ++j)
+    #pragma unroll
+                        for (int q = 0; q < C; ++q) mw[j][q] = w[j][q] >= 0 ? d.mask[w[j][q]] : ~0ull;
+                }
                 bool more = false;
     #pragma unroll
                 for (int j = 0; j < K; ++j) {

@@ -74,3 +74,69 @@ def test_last_rounds_of_a_batch(per_graph):
             for ref in refs:
                 sizes[:len(ref.wl_sizes)] += np.asarray(ref.wl_sizes)
             assert list(res.wl_sizes) == sizes.tolist()
+
+
+def stars_on_a_path(stars, n):
+    """A path of n nodes with `stars` centers of degree 33 to 35 spread over it: wide nodes, the others of class L."""
+    gap = n // stars
+    c = np.repeat(np.arange(stars) * gap + gap // 2, 33)
+    leaf = (c + 2 + np.tile(np.arange(33), stars) * 7) % n
+    return gg.from_pairs(n, np.concatenate([np.arange(n - 1), c]), np.concatenate([np.arange(1, n), leaf]), "%d stars" % stars)
+
+
+# Pushes of class L by tags or by masks: the rule's line is a 64th of the nodes being wide.
+@pytest.mark.parametrize("g", [stars_on_a_path(200, 12800), stars_on_a_path(201, 12800), stars_on_a_path(1, 20011),
+                               gg.erdos_renyi(20011, 20.0, gg.key(75, 0)), gg.erdos_renyi(20011, 26.0, gg.key(75, 1))],
+                         ids=lambda g: "%s_%d" % (g.name, g.m))
+def test_light_pushes(g):
+    import paper_1912_01478_amd as ip
+    ref = oracle.color_graph(g.rowptr, g.colidx)
+    print("[gpu] light pushes %s n=%d m=%d" % (g.name, g.n, g.m), flush=True)
+    for rowptr, colidx in ((g.rowptr, g.colidx), gg.shuffle_rows(g, 3)):
+        rp, ci = torch.from_numpy(np.ascontiguousarray(rowptr)).cuda(), torch.from_numpy(np.ascontiguousarray(colidx)).cuda()
+        for kw in (dict(), dict(mode="data"), dict(mode="topology"), dict(mode="rebuild"), dict(light="push", workgroups=70)):
+            res = ip.color_graph(rp, ci, **kw)
+            assert res.rounds == ref.rounds and np.array_equal(res.colors.cpu().numpy(), ref.colors), kw
+        out = torch.empty(g.n, dtype=torch.int32, device="cuda")
+        res = ip.color_graph_noalloc(rp, ci, out=out)
+        assert res.rounds == ref.rounds and np.array_equal(out.cpu().numpy(), ref.colors)
+
+
+@pytest.mark.parametrize("graphs", [63, 64, 80])
+def test_unions_of_many_graphs(graphs):
+    """From 64 graphs on, with a grid of 64 workgroups or more in eighths, each part of a union stays on one XCD."""
+    import paper_1912_01478_amd as ip
+    gs = [gg.erdos_renyi(1200 + 37 * k, 6.0 + k % 9, gg.key(76, k)) if k % 3 else gg.rmat(10, 10, gg.key(76, k)) for k in range(graphs)]
+    gs[5], gs[graphs - 1] = gg.empty(0), gg.star(3000, 0)
+    refs = [oracle.color_graph(g.rowptr, g.colidx) for g in gs]
+    node_off, edge_off, rp, ci = ip.pack_graphs([(g.rowptr, g.colidx) for g in gs])
+    rp, ci = torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda()
+    print("[gpu] union of %d graphs" % graphs, flush=True)
+    for kw in (dict(workgroups=64), dict(workgroups=72, mode="data"), dict(workgroups=64, mode="topology"), dict(workgroups=64, mode="rebuild"),
+               dict(workgroups=64, trace=True), dict(workgroups=68), dict(workgroups=64, per_graph=True), dict(workgroups=64, light="push")):
+        res = ip.color_graphs_batched(rp, ci, node_off, edge_off, **kw)
+        for k, (g, ref) in enumerate(zip(gs, refs)):
+            assert np.array_equal(res.graph(k).cpu().numpy(), ref.colors), (g.name, kw)
+            assert res.rounds[k] == ref.rounds, (g.name, kw)
+
+
+# The W/M cut-off chosen by size, full validation's entry search, and long rows left to the wavefront: rows at and past
+# 512, 2048 and 64 entries, empty rows between them, sorted or not.
+@pytest.mark.parametrize("g", [gg.star(2048, 1), gg.star(2049, 1), gg.star(13000, 6000), gg.rmat(15, 24, gg.key(74, 0), n=20011),
+                               gg.complete_bipartite(200, 10500), gg.empty(20000)], ids=lambda g: g.name)
+def test_long_rows_with_full_validation(g):
+    import paper_1912_01478_amd as ip
+    ref = oracle.color_graph(g.rowptr, g.colidx)
+    print("[gpu] long rows %s n=%d m=%d" % (g.name, g.n, g.m), flush=True)
+    for rowptr, colidx in ((g.rowptr, g.colidx), gg.shuffle_rows(g, 3)):
+        rp, ci = torch.from_numpy(np.ascontiguousarray(rowptr)).cuda(), torch.from_numpy(np.ascontiguousarray(colidx)).cuda()
+        for kw in (dict(), dict(validate=ip.VALIDATE_FULL), dict(validate=ip.VALIDATE_FULL, hub_min_degree=512)):
+            res = ip.color_graph(rp, ci, **kw)
+            assert res.rounds == ref.rounds and np.array_equal(res.colors.cpu().numpy(), ref.colors), kw
+    if g.m:  # one entry changed: no longer symmetric, or no longer in range
+        bad = ci.clone()
+        v = int(torch.argmax(rp[1:] - rp[:-1]))
+        bad[int(rp[v]) + 1] = bad[int(rp[v])]
+        with pytest.raises(ip.IpgcError) as e:
+            ip.color_graph(rp, bad, validate=ip.VALIDATE_FULL)
+        assert e.value.code == ip.EBADCSR
