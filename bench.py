@@ -63,7 +63,8 @@ UNIT_BYTES = {"assign_nodes": 16, "pull_entries": 8, "map_bytes": 1, "conflict_n
               "conflict_entries": 8, "list_writes": 4, "push_entries": 13, "commits": 0}
 
 PROFILE_DIR = os.path.join(ROOT, "profiles")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1912_01478_amd", "csrc", f) for f in ("ipgc_device.hpp", "ipgc.hip")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1912_01478_amd", "csrc", f) 
+                  for f in ("ipgc_device.hpp", "ipgc_core.hpp", "ipgc_small.hpp", "ipgc.hip")]
 NAMES = {1: "er_n10000_d8", 2: "rmat_s22_ef16", 3: "road_knn_n24000000", 4: "batch4096_er_rmat_n1e3_1e6",
          5: "serving2000_c4mix_10pct_rmat_s20"}
 

@@ -22,10 +22,14 @@
 //   k_rounds      every round (from round 2 after k_round1_light), one
 //                 cooperative launch with grid barriers (or k_assign_round +
 //                 k_conflict_round + k_push_round per round when stepped)
+//   k_core_rank, k_core_build, k_core_rounds  the rounds from at most 1024
+//                 uncolored nodes on, one workgroup (ipgc_core.hpp)
 // and read back the round count.  The host synchronizes after k_fill_static
 // (class counts decide the launches that follow; a node's row is only read
 // through its own checked row pointers), after the ring building when there is
 // one (the column checks decide whether to go on) and after the rounds.
+// Graphs of at most 10 240 nodes, alone or in a batch, are checked and colored by
+// one workgroup each instead, in one launch (k_small, ipgc_small.hpp).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

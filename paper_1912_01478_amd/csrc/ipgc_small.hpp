@@ -4,8 +4,8 @@
 // dependent loads from memory), and a call adds six launches and two host waits.  Here a graph of at most
 // kSmallNodes nodes is checked and colored in one launch: while more than kCore nodes are uncolored, rounds
 // walk a worklist with the colors, the forbidden-color masks and both lists in shared memory (only the
-// rows come from memory, mostly the L2); then the uncolored nodes go on in the core (ipgc_core.hpp).
-// Graphs of up to kCore nodes start there.  A batch runs a workgroup per graph, largest first.
+// rows come from memory, mostly the L2); then the uncolored nodes go on in the core (ipgc_core.hpp) or, in
+// graphs without long rows, in the row rounds below.  Graphs of up to kCore (kRowsNodes) nodes start there.  A batch runs a workgroup per graph, largest first.
 #pragma once
 
 #include "ipgc_core.hpp"
