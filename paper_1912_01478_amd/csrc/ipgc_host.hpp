@@ -15,7 +15,7 @@
 namespace ipgc {
 
 constexpr int kDefaultLightMax = 32;
-constexpr int kDefaultHubMin = 1024;
+constexpr int kDefaultHubMin = 1024;    // servers, and scratch without room for the cut-off by size
 constexpr int kPartsGraphs = 64;        // graphs of a union from which its parts stay on one XCD each (8 a part)
 constexpr int kDefaultTailGroups = 32;  // workgroups kept for small data-driven rounds (0: all)
 
