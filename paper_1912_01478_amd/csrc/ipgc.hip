@@ -848,6 +848,7 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
         TRY(read_counters(ws, s));
         int rc = row_verdict(*ws.host_ct, m);
         if (rc == IPGC_OK && ws.host_ct->bad_ids) rc = fail(IPGC_EBADCSR, "a column id is outside [0, n)");
+        if (rc == IPGC_OK && ws.host_ct->small_limit) rc = fail(IPGC_ELIMIT, "rounds did not finish");
         if (rc != IPGC_OK)
             for (int64_t g = 0; g < graphs; ++g) out_rounds[g] = -1;
         else
@@ -916,6 +917,7 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
         DevT<int64_t> d{};
         setup(d);
         TRY(run(ws, dev, s, P, d, n, m, n_union, grid, coop, &rounds, trace));
+        if (ws.host_ct->small_limit) return fail(IPGC_ELIMIT, "rounds did not finish");
     }
     HIP_TRY(hipMemcpyAsync(out_rounds, ws.grounds.p, sizeof(int32_t) * graphs, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));

@@ -149,6 +149,7 @@ struct Counters {
     int32_t tail_round;               // round from which the rounds go on in k_core_rounds (0: none left to it)
     int32_t tail_writers;             // workgroups that wrote that round's worklist
     int32_t tail_nodes;               // its nodes
+    int32_t small_limit;              // a graph of k_small was not finished after as many rounds as it has nodes
     int64_t ends[2];
 };
 

@@ -21,9 +21,18 @@ constexpr int kSmallNodes = 10240;
 // nodes and 5.3e4 entries, 256 / 258 / 251 / 277.
 constexpr int kSmallLight = 128;
 
+// A node's state in the list rounds.  Conflict tests look at the nodes that were uncolored when the round began
+// (tentative, or committed in this very round: kFresh): the smallest of them wins whatever its row says, so every
+// round has a winner.  Nodes committed before (kPast) are in the masks of the nodes in their own rows; a row that
+// names one of those without being named back (a one-way entry, which the default checks let through) must not
+// lose to it round after round.
+constexpr int kHeld = 0x3FFF;   // the color: at most 65 + kSmallNodes
+constexpr int kFresh = 0x4000;
+constexpr int kPast = 0x8000;
+
 struct SmallLists {
     uint64_t mask[kSmallNodes];     // bit t - 1: a committed neighbour has color t (t <= 64)
-    int16_t c[kSmallNodes];         // > 0 committed, -t tentative
+    uint16_t c[kSmallNodes];        // color, tentative or committed, and for committed nodes when (kFresh, kPast)
     uint16_t wl[2][kSmallNodes];    // worklists: short rows from the front, long rows from the back
 };
 
@@ -86,11 +95,12 @@ struct SmallRow {
 
 // First free color above 64 of node v, whose mask is full.
 __device__ __forceinline__ int32_t small_pull(const SmallShared &sh, const SmallArgs &, const int32_t *rp, const int32_t *ci, int v) {
-    for (int32_t x = max(kMaskColors + 1, -(int32_t)sh.a.c[v]);; x += 64) {
+    for (int32_t x = max(kMaskColors + 1, (int32_t)sh.a.c[v]);; x += 64) {
         uint64_t m = 0;
         for (int32_t k = rp[v]; k < rp[v + 1]; ++k) {
-            const uint32_t q = (uint32_t)((int32_t)sh.a.c[ci[k]] - x);
-            if (q < 64) m |= 1ull << q;
+            const int c = sh.a.c[ci[k]];
+            const uint32_t q = (uint32_t)((c & kHeld) - x);
+            if ((c & (kFresh | kPast)) && q < 64) m |= 1ull << q;
         }
         if (m != ~0ull) return x + __ffsll((unsigned long long)~m) - 1;
     }
@@ -125,7 +135,7 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            t[j] = v[j] >= 0 ? -(int)sh.a.c[v[j]] : 0;
+            t[j] = v[j] >= 0 ? (int)sh.a.c[v[j]] : 0;
             const Bounds<int32_t> row = v[j] >= 0 ? row_of(rp, v[j]) : Bounds<int32_t>{0, 0};
             b[j] = row.b;
             e[j] = row.e;
@@ -147,7 +157,7 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
 #pragma unroll
                 for (int q = 0; q < C; ++q) {
                     if (u[j][q] >= v[j]) past |= sorted;
-                    else if (abs((int)sh.a.c[u[j][q]]) == t[j]) lose |= 1u << j;
+                    else if ((sh.a.c[u[j][q]] & ~kFresh) == t[j]) lose |= 1u << j;
                 }
                 if (past || (lose >> j & 1u) || b[j] + q0 + C >= e[j]) done |= 1u << j;
             }
@@ -158,7 +168,7 @@ __device__ __forceinline__ void small_light(SmallShared &sh, const int32_t *rp, 
             const int at = wave_append(l, &sh.nl[p ^ 1]);
             if (l) nxt[at] = (uint16_t)v[j];
             if (v[j] < 0 || l) continue;
-            sh.a.c[v[j]] = (int16_t)t[j];
+            sh.a.c[v[j]] = (uint16_t)(t[j] | kFresh);
             out[v[j]] = t[j];
             gone += e[j] - b[j];
         }
@@ -190,7 +200,7 @@ __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, c
     for (int i0 = 0; i0 < nw; i0 += per) {  // the same for the whole workgroup
         const int i = i0 + (int)threadIdx.x / S;
         const int v = i < nw ? (int)cur[kSmallNodes - 1 - i] : -1;
-        const int t = v >= 0 ? -(int)sh.a.c[v] : 0, b = v >= 0 ? rp[v] : 0, e = v >= 0 ? rp[v + 1] : 0;
+        const int t = v >= 0 ? (int)sh.a.c[v] : 0, b = v >= 0 ? rp[v] : 0, e = v >= 0 ? rp[v + 1] : 0;
         bool lose = false, more = b < e;
         for (int k0 = b; __ballot(more); k0 += C * S) {  // the same for the whole wavefront
             int u[C];
@@ -203,7 +213,7 @@ __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, c
 #pragma unroll
             for (int q = 0; q < C; ++q) {
                 if (u[q] >= v) past |= sorted;
-                else hit |= abs((int)sh.a.c[u[q]]) == t;
+                else hit |= (sh.a.c[u[q]] & ~kFresh) == t;
             }
             lose = lose || (__ballot(hit) & gm) != 0;
             more = more && !lose && !(__ballot(past) & gm) && k0 + C * S < e;
@@ -213,7 +223,7 @@ __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, c
         if (l) nxt[kSmallNodes - 1 - at] = (uint16_t)v;
         if (v < 0 || lose) continue;
         if (gl == 0) {
-            sh.a.c[v] = (int16_t)t;
+            sh.a.c[v] = (uint16_t)(t | kFresh);
             out[v] = t;
             gone += e - b;
         }
@@ -234,8 +244,9 @@ __device__ __forceinline__ void small_wide(SmallShared &sh, const int32_t *rp, c
 // worklist p.  Up to four nodes a thread, each with its rank, its row and the colors it may not take.  A round has
 // two steps: conflict (a smaller neighbour with the same color in |s|; winners turn their s positive at once, which
 // changes no test) and, for the losers, the colors that neighbours have committed, whose entries leave the row.
+// Returns the number of the last round, 0 if the rounds did not end.
 __device__ __forceinline__ int32_t small_rows(SmallShared &sh, const SmallArgs &a, const int32_t *rp, const int32_t *ci,
-                                              int32_t m, int32_t *out, int p, int32_t r, int nact, bool fresh, bool sorted) {
+                                              int32_t n, int32_t m, int32_t *out, int p, int32_t r, int nact, bool fresh, bool sorted) {
     constexpr int K = kRowsNodes / kCore;
     const int tid = threadIdx.x, lane = lane_id();
     const bool keep = a.trace != nullptr;
@@ -299,6 +310,7 @@ __device__ __forceinline__ int32_t small_rows(SmallShared &sh, const SmallArgs &
 #pragma unroll
     for (int j = 0; j < K; ++j) act |= (v[j] >= 0 ? 1u : 0u) << j;
     for (; nact > 0; ++r) {
+        if (r > n) return 0;
         if (keep && tid == 0 && r - 1 < a.trace_cap) {
             a.trace[r - 1] = nact;
             a.trace_deg[r - 1] = degsum;
@@ -361,6 +373,11 @@ __device__ __forceinline__ int32_t small_rows(SmallShared &sh, const SmallArgs &
         core_sync();
     }
     return r - 1;
+}
+
+// More rounds than nodes.  (One graph alone: the host finds `finished` unset.)
+__device__ __forceinline__ void limit(const SmallArgs &a) {
+    if (threadIdx.x == 0) a.ct->small_limit = 1;
 }
 
 static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
@@ -449,7 +466,7 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
             const bool has = v < n, wide = has && rp[v + 1] - rp[v] > kSmallLight;
             if (has) {
                 sh.a.mask[v] = 0;
-                sh.a.c[v] = -1;
+                sh.a.c[v] = 1;
             }
             const int at = wave_append(has && !wide, &sh.nl[0]), aw = wave_append(wide, &sh.nw[0]);
             if (wide) sh.a.wl[0][kSmallNodes - 1 - aw] = (uint16_t)v;
@@ -457,17 +474,27 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
         }
         if (tid == 0) sh.deg = (unsigned long long)m;
         __syncthreads();
+        int pl = 0, pw = 0;  // entries of the round before's lists
         while (nact > kCore) {
             if (keep && tid == 0 && r - 1 < a.trace_cap) {
                 a.trace[r - 1] = nact;
                 a.trace_deg[r - 1] = (int64_t)sh.deg;
             }
             const int nl = sh.nl[p], nw = sh.nw[p];
+            if (r > n) {  // every round has a winner (unless ids that nobody checked lead outside the graph)
+                limit(a);
+                return;
+            }
             if (r > 1) {  // round 1's tentative colors are all 1
+                for (int i = tid; i < pl + pw; i += kCore) {  // the round before's list: its winners
+                    const int v = i < pl ? sh.a.wl[p ^ 1][i] : sh.a.wl[p ^ 1][kSmallNodes - 1 - (i - pl)];
+                    const int c = sh.a.c[v];
+                    if (c & kFresh) sh.a.c[v] = (uint16_t)(c ^ (kFresh | kPast));
+                }
                 for (int i = tid; i < nl + nw; i += kCore) {
                     const int v = i < nl ? sh.a.wl[p][i] : sh.a.wl[p][kSmallNodes - 1 - (i - nl)];
                     const uint64_t free = ~sh.a.mask[v];
-                    sh.a.c[v] = (int16_t)-(free ? __ffsll((unsigned long long)free) : small_pull(sh, a, rp, ci, v));
+                    sh.a.c[v] = (uint16_t)(free ? __ffsll((unsigned long long)free) : small_pull(sh, a, rp, ci, v));
                 }
             }
             if (tid == 0) sh.nl[p ^ 1] = sh.nw[p ^ 1] = 0;
@@ -479,6 +506,8 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
             if (lane == 0 && gone) atomicAdd(&sh.deg, 0ull - (unsigned long long)gone);
             core_sync();
             p ^= 1;
+            pl = nl;
+            pw = nw;
             ++r;
             nact = sh.nl[p] + sh.nw[p];
             core_sync();  // the counts are cleared in the next round, the degree sum read
@@ -488,7 +517,11 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
         deg = (int64_t)sh.deg;
     }
     if (rows) {
-        const int32_t last = small_rows(sh, a, rp, ci, (int32_t)m, out, p, r, nact, n <= kRowsNodes && r == 1, sorted);
+        const int32_t last = small_rows(sh, a, rp, ci, n, (int32_t)m, out, p, r, nact, n <= kRowsNodes && r == 1, sorted);
+        if (last == 0 && n > 0) {
+            limit(a);
+            return;
+        }
         if (tid == 0) {
             if (a.grounds) a.grounds[g] = last;
             if (!a.node_off) {
@@ -505,7 +538,7 @@ static __global__ __launch_bounds__(kCore) void k_small(SmallArgs a) {
         const int nl = sh.nl[p];
         int v = -1;
         if (tid < nact) v = tid < nl ? sh.a.wl[p][tid] : sh.a.wl[p][kSmallNodes - 1 - (tid - nl)];
-        const int32_t t = v >= 0 ? -(int32_t)sh.a.c[v] : 0;
+        const int32_t t = v >= 0 ? (int32_t)sh.a.c[v] : 0;
         const uint64_t mask = v >= 0 ? sh.a.mask[v] : 0;
         if (v >= 0) {
             atomicOr((unsigned long long *)&sh.bits[v >> 6], 1ull << (v & 63));

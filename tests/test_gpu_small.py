@@ -129,3 +129,49 @@ def test_verdicts():
                 ip.color_graphs_batched(*dev(prp, pci), node_off, edge_off)
             assert e.value.code == ip.EBADCSR, (which, at, value)
     check(g)
+
+
+def one_way(n, d, kind, seed):
+    """CSR whose rows need not be named back, all sorted: `d` random ids, ids below or above the row's, or the `d` ids
+    just below it."""
+    rng = np.random.default_rng(seed)
+    rows = []
+    for v in range(n):
+        if kind == "band":
+            ids = np.arange(max(0, v - d), v)
+        else:
+            lo, hi = {"any": (0, n), "below": (0, v), "above": (v + 1, n)}[kind]
+            ids = np.unique(rng.integers(lo, hi, d)) if hi > lo else np.arange(0)
+        rows.append(ids[ids != v])
+    rp = np.zeros(n + 1, dtype=np.int32)
+    rp[1:] = np.cumsum([len(r) for r in rows])
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+# Rows of over 63 entries, so that the lists hand over to the core: a color per node that its row's nodes of the same
+# round do not share is all that such input gets, but the rounds end, the same way every time, and nobody else's colors
+# change.
+@pytest.mark.parametrize("kind, n, d", [("any", 3000, 100), ("any", 10240, 30), ("below", 3000, 70), ("above", 3000, 80), ("band", 1300, 70)])
+def test_long_one_way_rows_end(kind, n, d):
+    import paper_1912_01478_amd as ip
+    rowptr, colidx = one_way(n, d, kind, n + d)
+    if kind == "any" and d == 30:  # one long row
+        colidx = np.concatenate([np.arange(1, 101, dtype=np.int32), colidx[rowptr[1]:]])
+        rowptr[1:] += 100 - rowptr[1]
+    rp, ci = dev(rowptr, colidx)
+    print("[gpu] one-way %s n=%d m=%d" % (kind, n, ci.numel()), flush=True)
+    first = ip.color_graph(rp, ci)
+    col = first.colors.cpu().numpy()
+    assert 1 <= first.rounds <= n and col.min() >= 1 and col.max() <= first.rounds
+    out = torch.empty(n, dtype=torch.int32, device="cuda")
+    for res in (ip.color_graph(rp, ci, mode="data", trace=True), ip.color_graph_noalloc(rp, ci, out=out)):
+        assert res.rounds == first.rounds and np.array_equal(res.colors.cpu().numpy(), col)
+    others = [SIZES[8], SHAPES[1], gg.erdos_renyi(20011, 9.0, gg.key(86, 0))]
+    for k in (2, 3):  # without and with a larger graph
+        graphs = [(g.rowptr, g.colidx) for g in others[:k]]
+        node_off, edge_off, prp, pci = ip.pack_graphs(graphs[:1] + [(rowptr, colidx)] + graphs[1:])
+        res = ip.color_graphs_batched(*dev(prp, pci), node_off, edge_off)
+        assert res.rounds[1] == first.rounds and np.array_equal(res.graph(1).cpu().numpy(), col)
+        for q, g in zip([0] + list(range(2, k + 1)), others):
+            ref = oracle.color_graph(g.rowptr, g.colidx)
+            assert res.rounds[q] == ref.rounds and np.array_equal(res.graph(q).cpu().numpy(), ref.colors)
