@@ -148,10 +148,11 @@ def one_way(n, d, kind, seed):
     return rp, np.concatenate(rows).astype(np.int32)
 
 
-# Rows of over 63 entries, so that the lists hand over to the core: a color per node that its row's nodes of the same
+# Rows of over 63 entries, so that the lists hand over to the core, or of 33 to 63, to the row rounds: a color per node that its row's nodes of the same
 # round do not share is all that such input gets, but the rounds end, the same way every time, and nobody else's colors
 # change.
-@pytest.mark.parametrize("kind, n, d", [("any", 3000, 100), ("any", 10240, 30), ("below", 3000, 70), ("above", 3000, 80), ("band", 1300, 70)])
+@pytest.mark.parametrize("kind, n, d", [("any", 3000, 100), ("any", 10240, 30), ("below", 3000, 70), ("above", 3000, 80), ("band", 1300, 70),
+                                        ("any", 6000, 63), ("below", 3000, 63), ("band", 1500, 63), ("above", 5000, 40)])
 def test_long_one_way_rows_end(kind, n, d):
     import paper_1912_01478_amd as ip
     rowptr, colidx = one_way(n, d, kind, n + d)
@@ -175,3 +176,24 @@ def test_long_one_way_rows_end(kind, n, d):
         for q, g in zip([0] + list(range(2, k + 1)), others):
             ref = oracle.color_graph(g.rowptr, g.colidx)
             assert res.rounds[q] == ref.rounds and np.array_equal(res.graph(q).cpu().numpy(), ref.colors)
+
+
+# Rows of at most 32 entries after list rounds, of at most 63 from the first round on in the row rounds or the core: such
+# graphs read their own rows, so the oracle's colors hold whether rows are named back or not.
+@pytest.mark.parametrize("kind, n, d", [("any", 500, 5), ("any", 4096, 9), ("any", 4097, 4), ("any", 10240, 8), ("any", 10240, 32), ("any", 1000, 63),
+                                        ("below", 4000, 4), ("below", 10000, 4), ("below", 4200, 32), ("above", 10000, 20),
+                                        ("band", 700, 40), ("band", 4600, 8), ("band", 4200, 32)])
+def test_short_one_way_rows_match_the_oracle(kind, n, d):
+    import paper_1912_01478_amd as ip
+    rowptr, colidx = one_way(n, d, kind, n + d)
+    ref = oracle.color_graph(rowptr, colidx)
+    rng = np.random.default_rng(4)
+    for name, ids in (("sorted", colidx), ("unsorted", colidx[np.lexsort((rng.random(colidx.size), np.repeat(np.arange(n), np.diff(rowptr))))])):
+        rp, ci = dev(rowptr, ids)
+        print("[gpu] one-way %s n=%d m=%d %s" % (kind, n, ci.numel(), name), flush=True)
+        out = torch.empty(n, dtype=torch.int32, device="cuda")
+        node_off, edge_off, prp, pci = ip.pack_graphs([(SIZES[3].rowptr, SIZES[3].colidx), (rowptr, ids)])
+        batch = ip.color_graphs_batched(*dev(prp, pci), node_off, edge_off)
+        for rounds, col in [(r.rounds, r.colors) for r in (ip.color_graph(rp, ci), ip.color_graph(rp, ci, trace=True, mode="data"),
+                                                         ip.color_graph_noalloc(rp, ci, out=out))] + [(batch.rounds[1], batch.graph(1))]:
+            assert rounds == ref.rounds and np.array_equal(col.cpu().numpy(), ref.colors)
