@@ -31,13 +31,15 @@ struct CoreNode {
 
 // Global memory between the kernels of the core.
 struct CoreMem {
-    uint64_t *adj;     // [kCore][kCoreWords]: bit j of row i set iff nodes i > j (by rank) are neighbours
+    uint64_t *adj;     // [kCore][kCoreWords]: bit j of row i set iff node i's list names node j (by rank), j < i
+                       // unless every node reads its own row (core_own_rows)
     CoreNode *node;    // [kCore]
     int32_t *rank;     // per node id: its rank (valid for the uncolored nodes only)
 };
 
 struct CoreShared {
-    uint64_t adj[kCoreWords * kCoreStride];        // word w of row i at [w * kCoreStride + i]; symmetric
+    uint64_t adj[kCoreWords * kCoreStride];        // word w of row i at [w * kCoreStride + i]: the nodes that node i
+                                                   // may lose to or learn colors from
     uint64_t bucket[kCoreWords * kCoreBuckets];    // [w][h]: uncolored nodes of word w with tentative color h modulo 128
     uint64_t won[kCoreWords];                      // nodes that commit in this round
     uint64_t done[kCoreWords];                     // nodes committed in earlier rounds (their colors stay in t)
@@ -317,8 +319,16 @@ __global__ __launch_bounds__(kCore) void k_core_rank(D d, CoreMem cm) {
     if (blockIdx.x == 0 && threadIdx.x == 0) d.ct->tail_nodes = total;
 }
 
+// Graphs of class L alone: in every round a node reads its own row, so the matrix holds the rows as they are, and entries
+// that are not named back count as in the definition.  The other lists (rings) hold smaller neighbours only, and the
+// matrix is completed from its lower half.
+template <class D>
+__device__ __forceinline__ bool core_own_rows(const D &d) {
+    return d.light_pull == kPullOnly;
+}
+
 // Matrix row and color window of every node of the core, a workgroup each: the uncolored nodes among the
-// node's smaller neighbours (class L: its row; W and M: its ring, which holds every smaller neighbour
+// node's smaller neighbours (core_own_rows: all neighbours; class L: its row; W and M: its ring, which holds every smaller neighbour
 // not yet seen committed), and which of the 128 colors from its last tentative color on are taken
 // (color mask and byte map; class L when it pulls: its neighbours' colors).
 template <class D>
@@ -336,7 +346,7 @@ __global__ __launch_bounds__(kCore) void k_core_build(D d, CoreMem cm) {
     const bool light = deg <= d.light_max;
     const int32_t start = light ? 0 : d.lstart[v], len = light ? (int32_t)deg : d.llen[v];
     const int32_t gb = light ? d.base(v) : 0;  // rows hold ids local to the graph, rings global ones
-    const bool pull = light && d.light_pull != kPushAll;
+    const bool pull = light && d.light_pull != kPushAll, own = core_own_rows(d);
     const int32_t *list = light ? d.colidx : d.lower;
     constexpr int P = 4;
     for (int32_t k0 = 0; k0 < len; k0 += P * kCore) {
@@ -354,7 +364,7 @@ __global__ __launch_bounds__(kCore) void k_core_build(D d, CoreMem cm) {
         for (int j = 0; j < P; ++j) {
             if (u[j] < 0) continue;
             if (!(cu[j] & kDone)) {
-                if (u[j] >= v) continue;
+                if (own ? u[j] == v : u[j] >= v) continue;
                 const int q = cm.rank[u[j]];
                 atomicOr((unsigned long long *)&row[q >> 6], 1ull << (q & 63));
             } else if (pull) {  // a node of class L needs no color above 33
@@ -446,7 +456,7 @@ __global__ __launch_bounds__(kCore) void k_core_rounds(D d, CoreMem cm) {
     __syncthreads();
     const int64_t ds = wave_sum(s.deg);
     if (lane_id() == 0 && ds) atomicAdd(&sh.wdeg, (unsigned long long)ds);
-    core_mirror(sh, words);
+    if (!core_own_rows(d)) core_mirror(sh, words);
     __syncthreads();
     const int64_t degsum = (int64_t)sh.wdeg;
     __syncthreads();

@@ -140,3 +140,42 @@ def test_long_rows_with_full_validation(g):
         with pytest.raises(ip.IpgcError) as e:
             ip.color_graph(rp, bad, validate=ip.VALIDATE_FULL)
         assert e.value.code == ip.EBADCSR
+
+
+def one_way(n, d, kind, seed):
+    """CSR whose rows, of at most `d` ids each and sorted, need not be named back."""
+    rng = np.random.default_rng(seed)
+    rows = []
+    for v in range(n):
+        lo, hi = {"any": (0, n), "below": (0, v), "above": (v + 1, n), "band": (max(0, v - d), v)}[kind]
+        ids = np.arange(lo, hi) if kind == "band" else np.unique(rng.integers(lo, hi, d)) if hi > lo else np.arange(0)
+        rows.append(ids[ids != v])
+    rp = np.zeros(n + 1, dtype=np.int32)
+    rp[1:] = np.cumsum([len(r) for r in rows])
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+# Graphs of class L alone read their own rows in every round, the last ones too: the oracle's colors, named back or not.
+@pytest.mark.parametrize("kind, n, d", [("any", 10241, 3), ("any", 20011, 8), ("any", 30011, 32), ("below", 15000, 4), ("below", 20011, 30),
+                                        ("above", 20011, 20), ("band", 10500, 20)])
+def test_one_way_rows_of_light_nodes(kind, n, d):
+    import paper_1912_01478_amd as ip
+    rowptr, colidx = one_way(n, d, kind, n + d)
+    ref = oracle.color_graph(rowptr, colidx)
+    rng = np.random.default_rng(4)
+    shuffled = colidx[np.lexsort((rng.random(colidx.size), np.repeat(np.arange(n), np.diff(rowptr))))]
+    print("[gpu] one-way %s n=%d m=%d rounds=%d" % (kind, n, colidx.size, ref.rounds), flush=True)
+    rp = torch.from_numpy(rowptr).cuda()
+    for ids in (colidx, shuffled):
+        ci = torch.from_numpy(ids).cuda()
+        for kw in (dict(), dict(mode="data", trace=True), dict(mode="topology"), dict(mode="rebuild"), dict(light="pull", workgroups=70)):
+            res = ip.color_graph(rp, ci, **kw)
+            assert res.rounds == ref.rounds and np.array_equal(res.colors.cpu().numpy(), ref.colors), kw
+        out = torch.empty(n, dtype=torch.int32, device="cuda")
+        res = ip.color_graph_noalloc(rp, ci, out=out)
+        assert res.rounds == ref.rounds and np.array_equal(out.cpu().numpy(), ref.colors)
+    small = gg.erdos_renyi(2000, 6.0, gg.key(73, 0))  # every graph of the union of class L
+    node_off, edge_off, prp, pci = ip.pack_graphs([(small.rowptr, small.colidx), (rowptr, colidx)])
+    for kw in (dict(), dict(trace=True), dict(per_graph=True)):
+        res = ip.color_graphs_batched(torch.from_numpy(prp).cuda(), torch.from_numpy(pci).cuda(), node_off, edge_off, **kw)
+        assert res.rounds[1] == ref.rounds and np.array_equal(res.graph(1).cpu().numpy(), ref.colors), kw
