@@ -811,6 +811,8 @@ int batch_impl(int64_t graphs, const int64_t *node_off, const int64_t *edge_off,
     if (small_call(P) && !P.per_graph && !trace) {
         for (int64_t g = 0; g < graphs; ++g) {
             const int64_t ng = node_off[g + 1] - node_off[g], mg = edge_off[g + 1] - edge_off[g];
+            // its one row pointer would have to be both 0 and mg; nothing else looks at it when all others are small
+            if (ng == 0 && mg > 0) return fail(IPGC_EBADCSR, "rowptr is decreasing or outside [0, m]");
             if (!small_graph(ng, mg)) continue;
             small.push_back((int32_t)g);
             n_union -= ng;

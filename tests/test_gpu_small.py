@@ -197,3 +197,20 @@ def test_short_one_way_rows_match_the_oracle(kind, n, d):
         for rounds, col in [(r.rounds, r.colors) for r in (ip.color_graph(rp, ci), ip.color_graph(rp, ci, trace=True, mode="data"),
                                                          ip.color_graph_noalloc(rp, ci, out=out))] + [(batch.rounds[1], batch.graph(1))]:
             assert rounds == ref.rounds and np.array_equal(col.cpu().numpy(), ref.colors)
+
+
+@pytest.mark.parametrize("entries", [1, (3 << 17) + 1])
+def test_entries_of_a_graph_without_nodes(entries):
+    """A graph of no nodes cannot hold entries, however many; beside small graphs, and beside a larger one."""
+    import paper_1912_01478_amd as ip
+    g, h = gg.erdos_renyi(3000, 8.0, gg.key(87, 0)), gg.erdos_renyi(20000, 8.0, gg.key(87, 1))
+    for others in ([g], [g, h]):
+        node_off = np.cumsum([0, 0] + [x.n for x in others])
+        edge_off = np.cumsum([0, entries] + [x.m for x in others])
+        for only in (0, entries):  # what the graph's one row pointer says
+            rp = np.concatenate([[only]] + [x.rowptr for x in others]).astype(np.int32)
+            ci = np.concatenate([np.zeros(entries)] + [x.colidx for x in others]).astype(np.int32)
+            for kw in (dict(), dict(mode="topology"), dict(trace=True)):
+                with pytest.raises(ip.IpgcError) as e:
+                    ip.color_graphs_batched(*dev(rp, ci), node_off, edge_off, **kw)
+                assert e.value.code == ip.EBADCSR, (entries, only, kw)
