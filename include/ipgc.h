@@ -164,8 +164,13 @@ typedef struct ipgc_trace {
     int64_t capacity;    /* entries available in each array below */
     int32_t *wl_size;    /* |WL_r| at the start of round r (r = 0 .. rounds-1), may be NULL */
     int64_t *wl_degree;  /* sum of the degrees of the nodes in WL_r, may be NULL */
-    int8_t *topology;    /* 1 if round r ran topology-driven, 0 if data-driven, may be NULL (per-graph
-                            batches: 1 if at least one graph ran it topology-driven) */
+    int8_t *topology;    /* 1 if the schedule makes round r topology-driven (|WL_r| > H), 0 if data-driven, may
+                            be NULL (per-graph batches: 1 if at least one graph ran it topology-driven).
+                            With the default H, rounds that one workgroup runs on its own walk their worklist
+                            whatever the schedule says: graphs of at most 10 240 nodes and 393 216 entries,
+                            the rounds of at most 1024 uncolored nodes, and BFS levels of graphs of at most
+                            32 768 nodes and 196 608 entries.  TOPOLOGY and an H of the caller's own
+                            always sweep. */
     int64_t recorded;    /* out: min(rounds, capacity) */
     int32_t *topo_graphs; /* batches with IPGC_FLAG_PER_GRAPH: number of graphs that ran round r
                             topology-driven, may be NULL (other calls leave it untouched) */

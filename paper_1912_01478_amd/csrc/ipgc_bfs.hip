@@ -473,8 +473,10 @@ int bfs_impl(const int32_t *rowptr, const int32_t *colidx, int64_t n, int64_t m,
     d.bar = w.bar.p;
     TRY(barrier_limit_ticks(dev, P.barrier_ms, &d.bar_limit));
     TRY(clear(w.ctl.p, sizeof(BfsCtl), s));
-    // sweeps over every node are what TOPOLOGY asks for, and a wait limit of -1 gives up at the first barrier
-    const bool one = n <= kOneNodes && m <= kOneEntries && P.workgroups == 0 && P.mode != IPGC_MODE_TOPOLOGY && P.barrier_ms >= 0;
+    // sweeps over every node are what TOPOLOGY and a caller's own H ask for, and a wait limit of -1 gives up at the
+    // first barrier
+    const bool sweeps = P.mode == IPGC_MODE_TOPOLOGY || (P.threshold > 0 && H < n);
+    const bool one = n <= kOneNodes && m <= kOneEntries && P.workgroups == 0 && !sweeps && P.barrier_ms >= 0;
     if (!one) TRY(clear(w.bar.p, sizeof(Barrier), s));
     // the search reads no row when the checks fail, so the host waits once, at the end
     const int64_t work = n + (P.check_ids ? m / 8 : 0);

@@ -141,3 +141,13 @@ def test_bfs_checks_come_before_any_row_is_read():
             ip.bfs(bad, ci, 0)
         assert e.value.code == -3
     check(g, 0, "hybrid")
+
+
+@pytest.mark.parametrize("H", [1, 50, 19999, 20000])
+def test_small_graphs_sweep_below_a_callers_threshold(H):
+    """An H below the node count asks for sweeps over the grid; from there on no level is one."""
+    g = GRAPHS[8]
+    for source in (0, g.n - 1):
+        res = check(g, source, "hybrid", threshold=H)
+        assert res.topology == [int(s > H) for s in res.frontier_sizes]
+        check(g, source, "data", threshold=H)

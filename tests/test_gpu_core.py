@@ -179,3 +179,18 @@ def test_one_way_rows_of_light_nodes(kind, n, d):
     for kw in (dict(), dict(trace=True), dict(per_graph=True)):
         res = ip.color_graphs_batched(torch.from_numpy(prp).cuda(), torch.from_numpy(pci).cuda(), node_off, edge_off, **kw)
         assert res.rounds[1] == ref.rounds and np.array_equal(res.graph(1).cpu().numpy(), ref.colors), kw
+
+
+@pytest.mark.parametrize("H", [1, 500, 1023, 1024, 1025])
+@pytest.mark.parametrize("g", [gg.complete(1100), cliques(5, 205), gg.rmat(14, 12, gg.key(72, 0))], ids=lambda g: g.name)
+def test_last_rounds_wait_for_a_callers_threshold(g, H):
+    """A caller's H leaves the last rounds to one workgroup from min(H, 1024) nodes on."""
+    import paper_1912_01478_amd as ip
+    ref = oracle.color_graph(g.rowptr, g.colidx, H)
+    rp, ci = torch.from_numpy(g.rowptr).cuda(), torch.from_numpy(g.colidx).cuda()
+    print("[gpu] core %s n=%d m=%d H=%d" % (g.name, g.n, g.m, H), flush=True)
+    for mode in ("hybrid", "data"):
+        res = ip.color_graph(rp, ci, mode=mode, threshold=H, trace=True)
+        assert res.rounds == ref.rounds and np.array_equal(res.colors.cpu().numpy(), ref.colors)
+        assert list(res.wl_sizes) == list(ref.wl_sizes) and list(res.wl_degrees) == list(ref.wl_degree_sums)
+        assert res.topology == (list(ref.topology) if mode == "hybrid" else [0] * ref.rounds)
