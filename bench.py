@@ -63,7 +63,7 @@ UNIT_BYTES = {"assign_nodes": 16, "pull_entries": 8, "map_bytes": 1, "conflict_n
               "conflict_entries": 8, "list_writes": 4, "push_entries": 13, "commits": 0}
 
 PROFILE_DIR = os.path.join(ROOT, "profiles")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1912_01478_amd", "csrc", f) 
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1912_01478_amd", "csrc", f)
                   for f in ("ipgc_device.hpp", "ipgc_core.hpp", "ipgc_small.hpp", "ipgc.hip")]
 NAMES = {1: "er_n10000_d8", 2: "rmat_s22_ef16", 3: "road_knn_n24000000", 4: "batch4096_er_rmat_n1e3_1e6",
          5: "serving2000_c4mix_10pct_rmat_s20"}
@@ -491,6 +491,9 @@ def run_workload(args, torch, pkg, w, steps, warmup, cpu):
                               "if the kernel source changed since), over the same time",
                 "work_bytes_per_launch": work_bytes / kd["launches"],
                 "work_GBps": round(work_bytes / kd["launches"] / (avg_us * 1e3), 1)}
+    if single and w.n <= 10240 and w.m <= 393216:
+        roofline["note"] = ("the profiled call, which these figures describe, runs the general path; a call with the default "
+                            "kernel options and no profile colors a graph of this size in one launch of k_small")
     ph = prof.profile.get("phase_ticks")
     if ph and len(ph) >= 4 and prof.profile.get("tick_khz"):
         r1_ms = (ph[3] - ph[0]) / prof.profile["tick_khz"]

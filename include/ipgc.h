@@ -74,11 +74,12 @@ typedef enum ipgc_mode {
  * remove self-loops and multi-edges first.  The kernels learn a node's forbidden
  * colors from pushes along its neighbours' rows, so on a CSR that is not
  * symmetric they would not follow the definition (which reads the node's own
- * row).  IPGC_VALIDATE_FULL rejects such input: every entry (v, u) needs its
+ * row).  Such a call still ends, if need be with IPGC_ELIMIT after as many rounds
+ * as nodes.  IPGC_VALIDATE_FULL rejects such input: every entry (v, u) needs its
  * reverse (u, v), and no row may hold v itself or the same id twice.  It sorts a
- * copy of every row in the library's workspace (rows already sorted are copied)
- * and looks each reverse entry up by binary search: O(m log max_degree) work on
- * the device, off the coloring's own path. */
+ * copy of every row in the library's workspace (if every row is sorted already,
+ * the rows are searched where they are) and looks each reverse entry up by binary
+ * search: O(m log max_degree) work on the device, off the coloring's own path. */
 enum {
     IPGC_VALIDATE_DEFAULT = 0, /* same as IPGC_VALIDATE_RANGES */
     IPGC_VALIDATE_NONE = 1,    /* trust the caller: only rowptr[0] == 0 and rowptr[n] == m are checked */
@@ -128,15 +129,24 @@ typedef struct ipgc_options {
     int32_t flags;             /* IPGC_FLAG_* */
     ipgc_profile *profile;     /* optional per-kernel timing and work counts (NULL: none) */
     int32_t workgroups;        /* workgroups of the round kernels (0: one per 1024 nodes or 3072 entries,
-                                  whichever is more, at most what the device keeps resident at once; larger values are clamped to that) */
+                                  whichever is more, at most what the device keeps resident at once;
+                                  larger values are clamped to that) */
     int32_t tail_workgroups;   /* once a data-driven round has at most 32 * tail_workgroups active nodes,
                                   only this many workgroups stay in the cooperative round loop (cheaper
-                                  grid barriers for the long tail of small rounds; 0: default, negative:
-                                  all workgroups stay) */
+                                  grid barriers for the long tail of small rounds; 0: default 32, negative:
+                                  all workgroups stay).  Rounds of at most 1024 nodes leave that loop
+                                  for one workgroup, so values up to 32 only matter where they do not:
+                                  IPGC_FLAG_RACY, servers, a threshold below 1024, a call's scratch
+                                  without room */
     int32_t barrier_timeout_ms; /* limit on every grid-barrier wait of a cooperative launch: a workgroup
                                   that waits longer gives up, every other one leaves at its next wait,
                                   and the call returns IPGC_EHIP (0: default 60000; -1: give up at the
-                                  first wait that does not complete at once, to exercise that path) */
+                                  first wait that does not complete at once, to exercise that path).
+                                  This field and the other kernel options (light_max_degree,
+                                  hub_min_degree, flags, workgroups, tail_workgroups, a threshold, a
+                                  profile, full validation), when set, keep small graphs on the round kernels that they
+                                  are about, which are two to five times as slow there as the one
+                                  workgroup that colors such a graph by default */
     int32_t reserved;          /* must be 0 */
 } ipgc_options;
 
@@ -241,7 +251,8 @@ int ipgc_color_graph_noalloc(const int32_t *csr_rowptr, const int32_t *csr_colid
  * the whole batch (topology-driven iff the batch's worklist exceeds H, by
  * default floor(6N/10) for N nodes in total).  Without a trace and with the
  * default kernel options, graphs of at most 10 240 nodes and 393 216 entries are
- * colored beside the union, a workgroup each, in HYBRID and DATA.
+ * colored beside the union, a workgroup each, in HYBRID and DATA; the worklist, N
+ * and H are then those of the others.
  *
  * With IPGC_FLAG_PER_GRAPH each graph g decides for itself (Section IV applied to
  * each graph): its round r is topology-driven iff its own worklist, its nodes not

@@ -162,7 +162,7 @@ struct Workspace {
         return IPGC_OK;
     }
 
-    // What a call can do without (132 KiB + 32 KiB): the last rounds then run in k_rounds.
+    // What a call can do without (128 KiB + 32 KiB): the last rounds then run in k_rounds.
     template <class Fn>
     int plan_core(Fn &&f) {
         TRY(f(core_adj, (int64_t)kCore * kCoreWords));
@@ -439,7 +439,11 @@ bool small_call(const Params &P) {
 
 // The entries up to which one workgroup is the faster one (against the general path): uniform, 10^4 nodes, 484
 // us against 767 at 3.2e5 entries, 1165 against 717 at 6.4e5; R-MAT, 8192 nodes, 931 against 973 at 3.7e5, 1388
-// against 1309 at 6.4e5; uniform, 1024 nodes, 239 against 343 at 9.5e4, 980 against 655 at 5.7e5.
+// against 1309 at 6.4e5; uniform, 1024 nodes, 239 against 343 at 9.5e4, 980 against 655 at 5.7e5.  In a batch the small
+// graphs run before the union of the others, as long as the longest of them takes; in the union they would share its
+// rounds.  Apart / in the union, beside a uniform graph of 3e5 nodes: one uniform graph of 10^4 nodes 994 / 1000 us, 64
+// of them 1010 / 1641, 256 R-MAT graphs of 10^4 nodes 1774 / 9973, but one R-MAT graph of 3.3e5 entries 1696 / 1420
+// (beside an R-MAT graph of 3e5 nodes 4719 / 4090, three of them 4525 / 4154).
 constexpr int64_t kSmallEntries = 3 << 17;
 
 bool small_graph(int64_t n, int64_t m) { return n <= kSmallNodes && m <= kSmallEntries; }
@@ -614,8 +618,8 @@ int run(Workspace &ws, int dev, hipStream_t s, const Params &P, D d, int64_t n, 
     const CoreMem cm{ws.core_adj.p, ws.core_node.p, ws.static_list.p};
     const bool core = coop > 0 && P.mode != IPGC_MODE_TOPOLOGY && !d.discard && !d.racy && cm.adj && cm.node;
     // A caller's own H asks for sweeps down to H nodes.  The default H of 60 % is below kCore for graphs of fewer than
-    // 1707 nodes alone, whose rounds run in the core all the same (uniform, 1200
-    // nodes and 6.4e5 entries: 1031 us, with sweeps down to 720 nodes 1576).
+    // 1707 nodes alone, whose rounds run in the core all the same (uniform, 1200 nodes and 6.4e5 entries: 1031 us, with
+    // sweeps down to 720 nodes 1576).
     const int32_t core_max = !core ? 0 : P.threshold > 0 ? (int32_t)std::min<int64_t>(kCore, H) : kCore;
     auto core_launch = [&](const auto &dv) -> int {
         using DV = std::decay_t<decltype(dv)>;

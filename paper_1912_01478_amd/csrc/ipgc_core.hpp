@@ -8,7 +8,7 @@
 //
 // What bounds them: nothing but the length of a round.  In k_rounds a round of this size takes 26
 // to 36 us (two or three grid barriers of 4 us and chains of dependent loads, whatever the number of
-// nodes); here it takes three workgroup barriers and reads of shared memory, 1 to 2 us.
+// nodes); here it takes three workgroup barriers and reads of shared memory, 4 to 5 us (R-MAT of 65 536 nodes, 88 rounds).
 #pragma once
 
 #include "ipgc_device.hpp"

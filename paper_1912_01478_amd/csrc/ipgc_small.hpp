@@ -5,7 +5,8 @@
 // kSmallNodes nodes is checked and colored in one launch: while more than kCore nodes are uncolored, rounds
 // walk a worklist with the colors, the forbidden-color masks and both lists in shared memory (only the
 // rows come from memory, mostly the L2); then the uncolored nodes go on in the core (ipgc_core.hpp) or, in
-// graphs without long rows, in the row rounds below.  Graphs of up to kCore (kRowsNodes) nodes start there.  A batch runs a workgroup per graph, largest first.
+// graphs without long rows, in the row rounds below.  Graphs of up to kCore (kRowsNodes) nodes start there.  A batch
+// runs a workgroup per graph, largest first.
 #pragma once
 
 #include <cstddef>
@@ -125,8 +126,8 @@ __device__ __forceinline__ int wave_append(bool flag, int *count) {
 // Graphs of class L alone (no row longer than this) learn the committed colors from the nodes' own rows, as the general
 // path does and as the definition reads them: their colors are the definition's also where a row names a node that does
 // not name it back, whose color no push brings.  Longer rows cost too much to read again in every round, and learn from
-// the neighbours' pushes.  Whole calls with pushes for all / own rows here / own rows up to
-// 63 entries: 10^4 nodes of degree 8 137 / 141 / 143 us, 1024 graphs of 10^3 to 10^4 nodes 1250 / 1264 / 1320.
+// the neighbours' pushes.  Whole calls with pushes for all / own rows here / own rows up to 63 entries: 10^4 nodes of
+// degree 8 137 / 141 / 143 us, 1024 graphs of 10^3 to 10^4 nodes 1250 / 1264 / 1320.
 constexpr int kOwnRows = 32;
 static_assert(kCore * kOwnRows <= kRowsEntries, "they go on in the row rounds");
 

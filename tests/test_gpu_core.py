@@ -194,3 +194,18 @@ def test_last_rounds_wait_for_a_callers_threshold(g, H):
         assert res.rounds == ref.rounds and np.array_equal(res.colors.cpu().numpy(), ref.colors)
         assert list(res.wl_sizes) == list(ref.wl_sizes) and list(res.wl_degrees) == list(ref.wl_degree_sums)
         assert res.topology == (list(ref.topology) if mode == "hybrid" else [0] * ref.rounds)
+
+
+@pytest.mark.parametrize("kind, n, d", [("any", 20011, 40), ("below", 12000, 70), ("above", 12000, 70)])
+def test_one_way_rows_with_wide_nodes_end(kind, n, d):
+    """Nodes above class L learn from pushes, so rows that are not named back get no definite colors; the call ends."""
+    import paper_1912_01478_amd as ip
+    rowptr, colidx = one_way(n, d, kind, n + d)
+    rp, ci = torch.from_numpy(rowptr).cuda(), torch.from_numpy(colidx).cuda()
+    print("[gpu] one-way wide %s n=%d m=%d" % (kind, n, colidx.size), flush=True)
+    for kw in (dict(), dict(mode="data", workgroups=9), dict(mode="topology")):
+        res = ip.color_graph(rp, ci, **kw)
+        assert 1 <= res.rounds <= n and int(res.colors.min()) >= 1
+    with pytest.raises(ip.IpgcError) as e:
+        ip.color_graph(rp, ci, validate=ip.VALIDATE_FULL)
+    assert e.value.code == ip.EBADCSR
