@@ -5,7 +5,7 @@ import pytest
 
 import graphgen as gg
 import oracle
-from tests.test_gpu_core import cliques
+from tests.test_gpu_core import cliques, one_way
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -129,23 +129,6 @@ def test_verdicts():
                 ip.color_graphs_batched(*dev(prp, pci), node_off, edge_off)
             assert e.value.code == ip.EBADCSR, (which, at, value)
     check(g)
-
-
-def one_way(n, d, kind, seed):
-    """CSR whose rows need not be named back, all sorted: `d` random ids, ids below or above the row's, or the `d` ids
-    just below it."""
-    rng = np.random.default_rng(seed)
-    rows = []
-    for v in range(n):
-        if kind == "band":
-            ids = np.arange(max(0, v - d), v)
-        else:
-            lo, hi = {"any": (0, n), "below": (0, v), "above": (v + 1, n)}[kind]
-            ids = np.unique(rng.integers(lo, hi, d)) if hi > lo else np.arange(0)
-        rows.append(ids[ids != v])
-    rp = np.zeros(n + 1, dtype=np.int32)
-    rp[1:] = np.cumsum([len(r) for r in rows])
-    return rp, np.concatenate(rows).astype(np.int32)
 
 
 # Rows of over 63 entries, so that the lists hand over to the core, or of 33 to 63, to the row rounds: a color per node that its row's nodes of the same
